@@ -279,8 +279,8 @@ int sweep_plain(const void* buf, size_t bytes, int K, int vec_width,
  * call hipMalloc: tight serving or measurement loops, harnesses that forbid
  * allocation).  Same arguments, kernels, validation and results as
  * sweep_plain, except:
- *  - The wave records, the cell result and the record offsets live in a
- *    static device array of 512 KiB + 256 bytes per GPU, held until the
+ *  - The wave records and the cell result live in a static device array
+ *    of 512 KiB + 256 bytes per GPU, held until the
  *    process ends; the call allocates nothing (no hipMalloc, hipFree, pinned
  *    host memory or events).  Its device address is resolved once per GPU,
  *    in sweep_init() or else on the first call on that GPU.

@@ -149,19 +149,29 @@ struct XcdSplitArgs {
 };
 
 // Per-cell result reduced on the device from the wave records.
-struct CellRes {
+struct alignas(16) CellRes {
   uint64_t sum;   // low 32 bits used
   uint64_t xr;    // low 32 bits used
   uint64_t tmin;
   uint64_t tmax;
 };
 
+// Folding of wave records into cell results: cell c owns records
+// [offsets[c], offsets[c+1]).  The offsets of one or two cells travel in the
+// argument block (`offsets` null); those of more lie where the device can
+// read them.  `out` is device or pinned host memory.
+struct FinishArgs {
+  const sweep_wave_rec_t* rec;
+  const uint64_t* offsets;
+  CellRes* out;
+  uint64_t few[3];
+};
+
 // ---- static scratch of the allocation-free entry point (static_scratch.hip)
-// Layout: per-wave records, then the cell result, then the two record
-// offsets the finishing kernel reads.  512 KiB + 256 bytes per device.
+// Layout: per-wave records, then the cell result.  512 KiB + 256 bytes per
+// device.
 constexpr uint64_t kStaticRecords = 16384;
 constexpr uint64_t kStaticResOffset = kStaticRecords * sizeof(sweep_wave_rec_t);
-constexpr uint64_t kStaticOffsOffset = kStaticResOffset + 64;
 constexpr uint64_t kStaticScratchBytes = kStaticResOffset + 256;
 // Device address of the calling thread's current device's copy of the
 // static scratch (resolved once per device, with that device current).
@@ -192,9 +202,8 @@ hipError_t launch_walkers(int policy, hipStream_t st, const WalkArgs& a);
 // ---- fill, finishing, clock, reduction (kernels_misc.hip)
 hipError_t launch_fill(uint32_t* buf, uint64_t n_words, uint64_t seed,
                        hipStream_t st);
-// One workgroup per cell: cell c owns records [offsets[c], offsets[c+1]).
-hipError_t launch_finish_cells(const sweep_wave_rec_t* rec, const uint64_t* offsets,
-                               uint32_t n_cells, CellRes* out, hipStream_t st);
+// One workgroup per cell.
+hipError_t launch_finish_cells(const FinishArgs& a, uint32_t n_cells, hipStream_t st);
 hipError_t launch_read_clock(uint64_t* out, hipStream_t st);
 // `loads` (4 or 8) 16-byte loads in flight per lane per iteration.
 const void* reduce_kernel(int dtype, int loads);

@@ -53,9 +53,7 @@ struct Dev {
   int clock_khz = 0, mem_khz = 0, bus_bits = 0;
   sweep_wave_rec_t* rec = nullptr;
   size_t rec_cap = 0;
-  CellRes* res = nullptr;
-  size_t res_cap = 0;
-  CellRes* res_h = nullptr;   // pinned host copy
+  CellRes* res_h = nullptr;   // cell results, pinned: the finishing kernel writes them
   size_t res_h_cap = 0;
   float* partials = nullptr;
   size_t partials_cap = 0;
@@ -64,9 +62,7 @@ struct Dev {
   uint64_t* clk = nullptr;
   uint64_t* chase_out = nullptr;  // 5 words per chase call
   uint64_t* walk_out = nullptr;   // 4 words per walker
-  uint64_t* offs = nullptr;     // per-cell record offsets (device)
-  size_t offs_cap = 0;
-  uint64_t* offs_h = nullptr;   // pinned staging copy
+  uint64_t* offs_h = nullptr;   // per-cell record offsets, pinned: the finish reads them
   size_t offs_h_cap = 0;
   std::vector<hipEvent_t> ev;
   hipStream_t capture = nullptr;
@@ -104,7 +100,7 @@ int ensure_host(T*& p, size_t& cap, size_t n) {
   p = nullptr;
   cap = 0;
   if (hipHostMalloc(reinterpret_cast<void**>(&p), std::max<size_t>(n, 1) * sizeof(T),
-                    hipHostMallocDefault) != hipSuccess) {
+                    hipHostMallocCoherent) != hipSuccess) {
     (void)hipGetLastError();
     return fail(SWEEP_ENOMEM, "pinned host allocation failed");
   }
@@ -124,7 +120,6 @@ int ensure_events(Dev& d, size_t n) {
 // Frees everything a Dev holds, then the Dev (its device is current).
 void release_device(Dev* d) {
   if (d->rec) (void)hipFree(d->rec);
-  if (d->res) (void)hipFree(d->res);
   if (d->res_h) (void)hipHostFree(d->res_h);
   if (d->partials) (void)hipFree(d->partials);
   if (d->dsum) (void)hipFree(d->dsum);
@@ -132,7 +127,6 @@ void release_device(Dev* d) {
   if (d->clk) (void)hipFree(d->clk);
   if (d->chase_out) (void)hipFree(d->chase_out);
   if (d->walk_out) (void)hipFree(d->walk_out);
-  if (d->offs) (void)hipFree(d->offs);
   if (d->offs_h) (void)hipHostFree(d->offs_h);
   for (auto e : d->ev) (void)hipEventDestroy(e);
   if (d->capture) (void)hipStreamDestroy(d->capture);
@@ -143,7 +137,6 @@ void release_device(Dev* d) {
 int setup_device(Dev* d) {
   // scratch for the largest default grid (32 waves per CU)
   SW_TRY(ensure_dev(d->rec, d->rec_cap, (size_t)d->num_cus * 32));
-  SW_TRY(ensure_dev(d->res, d->res_cap, 64));
   SW_TRY(ensure_host(d->res_h, d->res_h_cap, 64));
   size_t one = 0, one_h = 0, clk_cap = 0;
   SW_TRY(ensure_dev(d->dsum, one, 1));
@@ -304,20 +297,28 @@ hipError_t enqueue(const Prepared& p, hipStream_t st, sweep_wave_rec_t* rec,
   return launch_timed(p.fn, p.grid, p.threads, p.lds, st, a, e0, e1);
 }
 
-// Copies the record offsets of `n` cells (n + 1 entries) to the device.
-int upload_offsets(Dev& d, const std::vector<uint64_t>& offs, hipStream_t st) {
-  SW_TRY(ensure_host(d.offs_h, d.offs_h_cap, offs.size()));
-  SW_TRY(ensure_dev(d.offs, d.offs_cap, offs.size()));
-  std::copy(offs.begin(), offs.end(), d.offs_h);
-  HIP_TRY(hipMemcpyAsync(d.offs, d.offs_h, offs.size() * sizeof(uint64_t),
-                         hipMemcpyHostToDevice, st));
-  return SWEEP_OK;
-}
-
 std::vector<uint64_t> record_offsets(const std::vector<Prepared>& ps) {
   std::vector<uint64_t> o(ps.size() + 1, 0);
   for (size_t i = 0; i < ps.size(); ++i) o[i + 1] = o[i] + ps[i].plan.pub.waves;
   return o;
+}
+
+// The finishing launch's arguments for the cells whose records are split at
+// `offs` (n + 1 entries): up to two cells carry the offsets themselves, more
+// read them from the device's pinned copy.  Neither needs a copy in front of
+// the cells, whose two dispatch gaps cost a small cell about 20 us.
+int finish_args(Dev& d, const sweep_wave_rec_t* rec, const std::vector<uint64_t>& offs,
+                FinishArgs* out) {
+  FinishArgs a{rec, nullptr, d.res_h, {0, 0, 0}};
+  if (offs.size() <= 3) {
+    std::copy(offs.begin(), offs.end(), a.few);
+  } else {
+    SW_TRY(ensure_host(d.offs_h, d.offs_h_cap, offs.size()));
+    std::copy(offs.begin(), offs.end(), d.offs_h);
+    a.offsets = d.offs_h;
+  }
+  *out = a;
+  return SWEEP_OK;
 }
 
 void fill_result(const Dev& d, const Prepared& p, const CellRes& r, double ms,
@@ -393,16 +394,15 @@ int run_prepared(Dev& d, std::vector<Prepared>& ps, hipStream_t st,
   const size_t n = ps.size();
   const std::vector<uint64_t> offs = record_offsets(ps);
   if (!wave_out) SW_TRY(ensure_dev(d.rec, d.rec_cap, offs[n]));
-  SW_TRY(ensure_dev(d.res, d.res_cap, n));
   SW_TRY(ensure_host(d.res_h, d.res_h_cap, n));
   SW_TRY(ensure_events(d, 2 * n + 1));
   sweep_wave_rec_t* rec = wave_out ? wave_out : d.rec;
   if (wave_out && n != 1) return fail(SWEEP_EINVAL, "wave_out takes a single cell");
-  SW_TRY(upload_offsets(d, offs, st));
+  FinishArgs fin;
+  SW_TRY(finish_args(d, rec, offs, &fin));
   for (size_t i = 0; i < n; ++i)
     HIP_TRY(enqueue(ps[i], st, rec + offs[i], lane_out, d.ev[2 * i], d.ev[2 * i + 1]));
-  HIP_TRY(launch_finish_cells(rec, d.offs, (uint32_t)n, d.res, st));
-  HIP_TRY(hipMemcpyAsync(d.res_h, d.res, n * sizeof(CellRes), hipMemcpyDeviceToHost, st));
+  HIP_TRY(launch_finish_cells(fin, (uint32_t)n, st));
   HIP_TRY(hipEventRecord(d.ev[2 * n], st));
   HIP_TRY(hipEventSynchronize(d.ev[2 * n]));
   for (size_t i = 0; i < n; ++i) {
@@ -480,15 +480,13 @@ int xcd_run(Dev& d, const sweep_opts_t* opt, Prepared& p, uint64_t n_act, Args& 
   sweep_wave_rec_t* wave_out = opt ? opt->wave_out : nullptr;
   if (!wave_out) SW_TRY(ensure_dev(d.rec, d.rec_cap, n_act));
   a.rec = wave_out ? wave_out : d.rec;
-  SW_TRY(ensure_dev(d.res, d.res_cap, 1));
-  SW_TRY(ensure_host(d.res_h, d.res_h_cap, 1));
   SW_TRY(ensure_events(d, 3));
   hipStream_t st = as_stream(opt);
-  SW_TRY(upload_offsets(d, std::vector<uint64_t>{0, n_act}, st));
+  FinishArgs fin;
+  SW_TRY(finish_args(d, a.rec, {0ull, n_act}, &fin));
   HIP_TRY(launch_clear_records(a.rec, n_act, st));
   HIP_TRY(launch_timed(p.fn, p.grid, p.threads, p.lds, st, a, d.ev[0], d.ev[1]));
-  HIP_TRY(launch_finish_cells(a.rec, d.offs, 1, d.res, st));
-  HIP_TRY(hipMemcpyAsync(d.res_h, d.res, sizeof(CellRes), hipMemcpyDeviceToHost, st));
+  HIP_TRY(launch_finish_cells(fin, 1, st));
   HIP_TRY(hipEventRecord(d.ev[2], st));
   HIP_TRY(hipEventSynchronize(d.ev[2]));
   std::vector<sweep_wave_rec_t> h(n_act);
@@ -597,10 +595,10 @@ int two_stream_impl(const void* buf, size_t bytes, int depth, int waves_plain,
   a.rec = rec;
   a.lane_out = opt ? opt->lane_out : nullptr;
   hipStream_t st = as_stream(opt);
-  SW_TRY(upload_offsets(*d, {0ull, (uint64_t)wa, (uint64_t)wa + wb}, st));
+  FinishArgs fin;
+  SW_TRY(finish_args(*d, rec, {0ull, (uint64_t)wa, (uint64_t)wa + wb}, &fin));
   HIP_TRY(launch_timed(fn, grid, threads, lds, st, a, d->ev[0], d->ev[1]));
-  HIP_TRY(launch_finish_cells(rec, d->offs, 2, d->res, st));
-  HIP_TRY(hipMemcpyAsync(d->res_h, d->res, 2 * sizeof(CellRes), hipMemcpyDeviceToHost, st));
+  HIP_TRY(launch_finish_cells(fin, 2, st));
   HIP_TRY(hipEventRecord(d->ev[2], st));
   HIP_TRY(hipEventSynchronize(d->ev[2]));
   float ms = 0;
@@ -844,15 +842,12 @@ int sweep_plain_noalloc(const void* buf, size_t bytes, int K, int vec_width,
     return fail(SWEEP_EINVAL, "the launch's waves exceed the static scratch (16384 records)");
   sweep_wave_rec_t* rec = wave_out ? wave_out : reinterpret_cast<sweep_wave_rec_t*>(sp);
   CellRes* res = reinterpret_cast<CellRes*>(sp + kStaticResOffset);
-  uint64_t* offs = reinterpret_cast<uint64_t*>(sp + kStaticOffsOffset);
   hipStream_t st = as_stream(opt);
-  // every value the kernels read is written first in this call: the record
-  // offsets here, the records by the sweep kernel, the result by the finish
-  const uint64_t offs_h[2] = {0, waves};
+  // every value the kernels read is written first in this call: the records
+  // by the sweep kernel, the result by the finish
   CellRes r;
-  HIP_TRY(hipMemcpyAsync(offs, offs_h, sizeof(offs_h), hipMemcpyHostToDevice, st));
   HIP_TRY(enqueue(p, st, rec, opt ? opt->lane_out : nullptr, nullptr, nullptr));
-  HIP_TRY(launch_finish_cells(rec, offs, 1, res, st));
+  HIP_TRY(launch_finish_cells(FinishArgs{rec, nullptr, res, {0, waves, 0}}, 1, st));
   HIP_TRY(hipMemcpyAsync(&r, res, sizeof(r), hipMemcpyDeviceToHost, st));
   HIP_TRY(hipStreamSynchronize(st));
   fill_result(*d, p, r, 0.0, out);
@@ -866,12 +861,11 @@ struct sweep_graph {
   int ordinal = -1;
   std::vector<Prepared> ps;
   sweep_wave_rec_t* rec = nullptr;
-  CellRes* res = nullptr;
-  CellRes* res_h = nullptr;
+  CellRes* res_h = nullptr;     // pinned: the finishing node writes it
   uint64_t* offs = nullptr;
   FusedPoint* pts = nullptr;    // point lists of the fused launches
   size_t fused_launches = 0;
-  std::vector<hipEvent_t> ev;   // start, end, done of a launch
+  std::vector<hipEvent_t> ev;   // start, end of a launch
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
 };
@@ -884,7 +878,6 @@ void free_graph(sweep_graph* g) {
   if (g->graph) (void)hipGraphDestroy(g->graph);
   for (auto e : g->ev) (void)hipEventDestroy(e);
   if (g->rec) (void)hipFree(g->rec);
-  if (g->res) (void)hipFree(g->res);
   if (g->offs) (void)hipFree(g->offs);
   if (g->pts) (void)hipFree(g->pts);
   if (g->res_h) (void)hipHostFree(g->res_h);
@@ -977,9 +970,8 @@ int create_graph(Dev& d, const sweep_cell_t* cells, int n, const sweep_opts_t* o
   };
   const size_t n_rec = std::max<uint64_t>(offs.back(), 1);
   if (hipMalloc(reinterpret_cast<void**>(&g->rec), n_rec * sizeof(sweep_wave_rec_t)) != hipSuccess ||
-      hipMalloc(reinterpret_cast<void**>(&g->res), (size_t)n * sizeof(CellRes)) != hipSuccess ||
       hipMalloc(reinterpret_cast<void**>(&g->offs), offs.size() * sizeof(uint64_t)) != hipSuccess ||
-      hipHostMalloc(reinterpret_cast<void**>(&g->res_h), (size_t)n * sizeof(CellRes), hipHostMallocDefault) != hipSuccess) {
+      hipHostMalloc(reinterpret_cast<void**>(&g->res_h), (size_t)n * sizeof(CellRes), hipHostMallocCoherent) != hipSuccess) {
     (void)hipGetLastError();
     return fail_g(SWEEP_ENOMEM, "graph scratch allocation failed");
   }
@@ -1005,7 +997,7 @@ int create_graph(Dev& d, const sweep_cell_t* cells, int n, const sweep_opts_t* o
         hipStreamSynchronize(nullptr) != hipSuccess)
       return fail_g(SWEEP_EHIP, "graph record clear failed");
   }
-  g->ev.resize(3, nullptr);
+  g->ev.resize(2, nullptr);
   for (auto& e : g->ev)
     if (hipEventCreate(&e) != hipSuccess) return fail_g(SWEEP_EHIP, "hipEventCreate failed");
   if (!d.capture && hipStreamCreateWithFlags(&d.capture, hipStreamNonBlocking) != hipSuccess)
@@ -1029,7 +1021,8 @@ int create_graph(Dev& d, const sweep_cell_t* cells, int n, const sweep_opts_t* o
     ++g->fused_launches;
   }
   if (cap_err == hipSuccess)
-    cap_err = launch_finish_cells(g->rec, g->offs, (uint32_t)n, g->res, d.capture);
+    cap_err = launch_finish_cells(FinishArgs{g->rec, g->offs, g->res_h, {0, 0, 0}}, (uint32_t)n,
+                                  d.capture);
   hipError_t end_err = hipStreamEndCapture(d.capture, &g->graph);
   if (cap_err != hipSuccess || end_err != hipSuccess)
     return fail_g(SWEEP_EHIP, std::string("graph capture failed: ") +
@@ -1044,13 +1037,11 @@ int create_graph(Dev& d, const sweep_cell_t* cells, int n, const sweep_opts_t* o
 int launch_graph(Dev& d, sweep_graph* g, hipStream_t st, sweep_result_t* results,
                  double* graph_ms) {
   const size_t n = g->ps.size();
-  hipEvent_t e_start = g->ev[0], e_end = g->ev[1], e_done = g->ev[2];
+  hipEvent_t e_start = g->ev[0], e_end = g->ev[1];
   HIP_TRY(hipEventRecord(e_start, st));
   HIP_TRY(hipGraphLaunch(g->exec, st));
   HIP_TRY(hipEventRecord(e_end, st));
-  HIP_TRY(hipMemcpyAsync(g->res_h, g->res, n * sizeof(CellRes), hipMemcpyDeviceToHost, st));
-  HIP_TRY(hipEventRecord(e_done, st));
-  HIP_TRY(hipEventSynchronize(e_done));
+  HIP_TRY(hipEventSynchronize(e_end));
   float ms = 0;
   HIP_TRY(hipEventElapsedTime(&ms, e_start, e_end));
   if (graph_ms) *graph_ms = ms;
@@ -1199,12 +1190,12 @@ int sweep_reduce_fp(const void* payload, size_t n_elems, int dtype,
   a.partials = d->partials;
   a.rec = d->rec;
   hipStream_t st = as_stream(opt);
-  SW_TRY(upload_offsets(*d, {0ull, (uint64_t)grid * 4}, st));
+  FinishArgs fin;
+  SW_TRY(finish_args(*d, d->rec, {0ull, (uint64_t)grid * 4}, &fin));
   HIP_TRY(launch_timed(fn, grid, 256u, 0, st, a, d->ev[0], d->ev[1]));
   HIP_TRY(launch_reduce_finish(d->partials, grid, d->dsum, st));
-  HIP_TRY(launch_finish_cells(d->rec, d->offs, 1, d->res, st));
+  HIP_TRY(launch_finish_cells(fin, 1, st));
   HIP_TRY(hipMemcpyAsync(d->dsum_h, d->dsum, sizeof(double), hipMemcpyDeviceToHost, st));
-  HIP_TRY(hipMemcpyAsync(d->res_h, d->res, sizeof(CellRes), hipMemcpyDeviceToHost, st));
   HIP_TRY(hipEventRecord(d->ev[2], st));
   HIP_TRY(hipEventSynchronize(d->ev[2]));
   *sum = *d->dsum_h;

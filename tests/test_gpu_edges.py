@@ -10,7 +10,7 @@ if not torch.cuda.is_available():
 
 import numpy as np
 
-from gpu_util import dev_bytes, host_words
+from gpu_util import decode_recs, dev_bytes, host_words, recs
 from oracle import splitmix
 from paper_2608_15764_amd import ilpsweep as isw
 
@@ -28,3 +28,39 @@ def test_fill_at_chunk_edges(nbytes):
     torch.cuda.synchronize()
     assert np.array_equal(host_words(buf)[:nbytes // 4], splitmix.words(SEED, 0, nbytes // 4))
     assert not buf[nbytes:].any()
+
+
+@pytest.mark.parametrize("wgs", [1, 255, 256, 1023, 1024, 1025, 2048, 2049, 4096])
+def test_finish_folds_every_record(wgs):
+    """The cell result is the fold of its wave records, at the edges of the
+    finishing kernel's batches (4096 records) and of its threads."""
+    nbytes, waves = 1 << 20, 4 * wgs
+    buf = dev_bytes(nbytes)
+    isw.sweep_fill_u32(buf, nbytes, SEED + 1)
+    out = recs(waves)
+    L = 64 * waves + 64 * 3                  # an uneven deal, wrapping
+    print("finish", waves, "records", flush=True)
+    r = isw.sweep_plain(buf, nbytes, 1, 4, 4, L, isw.make_opts(grid_wgs=wgs, wave_out=out))
+    h = decode_recs(out)
+    assert r["waves"] == waves
+    assert r["sum32"] == int(h["sum32"].sum(dtype=np.uint64) & 0xFFFFFFFF)
+    assert r["xor32"] == int(np.bitwise_xor.reduce(h["xor32"]))
+    assert r["window_ticks"] == int(h["t1"].max() - h["t0"].min())
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 7])
+def test_cells_of_one_call_keep_apart(n):
+    """One or two cells carry their record offsets in the launch, more read
+    them from memory: the results are those of single calls either way."""
+    nbytes = 2 << 20
+    buf = dev_bytes(nbytes)
+    isw.sweep_fill_u32(buf, nbytes, SEED + 2)
+    cells = [isw.make_cell(buf, nbytes, 1 + i, 16, 4 * (1 + i % 3), nbytes // 16 + 4096 * i)
+             for i in range(n)]
+    many = isw.sweep_run(cells)
+    graph, _ = isw.sweep_batched(cells)
+    for c, a, b in zip(cells, many, graph):
+        one = isw.sweep_plain(buf, nbytes, c.K, 16, c.waves_per_cu, c.total_logical_loads)
+        assert (a["sum32"], a["xor32"]) == (b["sum32"], b["xor32"]) == (one["sum32"],
+                                                                       one["xor32"])
+        assert a["window_ticks"] > 0 and b["window_ticks"] > 0
