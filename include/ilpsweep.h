@@ -150,7 +150,9 @@ typedef struct {
                                       sgprs is 0: the runtime does not report it */
   uint64_t window_ticks;   /* max(t1) - min(t0) over all waves             */
   double   window_ns;      /* window_ticks converted with the clock rate   */
-  double   event_ms;       /* hipEvent time of the kernel's dispatch       */
+  double   event_ms;       /* hipEvent time of the kernel's dispatch: from the
+                              end of the call's previous cell, or for its
+                              first cell an event right before it          */
   double   gbps;           /* issued_bytes / window_ns                     */
 } sweep_result_t;
 

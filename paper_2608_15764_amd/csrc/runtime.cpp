@@ -64,6 +64,7 @@ struct Dev {
   uint64_t* walk_out = nullptr;   // 4 words per walker
   uint64_t* offs_h = nullptr;   // per-cell record offsets, pinned: the finish reads them
   size_t offs_h_cap = 0;
+  hipEvent_t start = nullptr;   // recorded before a call's first timed dispatch
   std::vector<hipEvent_t> ev;
   hipStream_t capture = nullptr;
   // kernel attributes and residency limit per (kernel, WG threads, LDS)
@@ -108,7 +109,10 @@ int ensure_host(T*& p, size_t& cap, size_t n) {
   return SWEEP_OK;
 }
 
+// The start event only marks a time, so it needs no fence to the host
+// (1.3 us of a single call).
 int ensure_events(Dev& d, size_t n) {
+  if (!d.start) HIP_TRY(hipEventCreateWithFlags(&d.start, hipEventDisableSystemFence));
   while (d.ev.size() < n) {
     hipEvent_t e;
     HIP_TRY(hipEventCreate(&e));
@@ -128,6 +132,7 @@ void release_device(Dev* d) {
   if (d->chase_out) (void)hipFree(d->chase_out);
   if (d->walk_out) (void)hipFree(d->walk_out);
   if (d->offs_h) (void)hipHostFree(d->offs_h);
+  if (d->start) (void)hipEventDestroy(d->start);
   for (auto e : d->ev) (void)hipEventDestroy(e);
   if (d->capture) (void)hipStreamDestroy(d->capture);
   delete d;
@@ -269,32 +274,42 @@ int prepare(Dev& d, const sweep_cell_t& c, int pin, Prepared* out, bool cache = 
   return SWEEP_OK;
 }
 
-// Launches kernel `fn` whose one parameter is the struct `a`.  With events,
-// hipExtLaunchKernel stamps them from the kernel's own dispatch (its start
-// and its end), with no marker packets between kernels; without (as under
-// graph capture), a plain launch.
+// Launches kernel `fn` whose one parameter is the struct `a`.  With `stop`,
+// hipExtLaunchKernel stamps it from the dispatch's own end.  A dispatch is
+// timed from the event before it in the stream: the end of the previous
+// timed dispatch, or for a call's first one `start`, recorded here.  (Asking
+// hipExtLaunchKernel for a start event as well costs a single call 13 us and
+// every dispatch of a sweep a gap of 5 us or more, since it stops the queue
+// around the kernel; the times agree to 0.1 us for a single dispatch, and
+// back to back they include the gap between two dispatches, 0.1-0.7 us:
+// 17.56 us stamped by itself, 17.64 from an event before it, 18.22 from the
+// end of the dispatch before it.)
 template <class Args>
 hipError_t launch_timed(const void* fn, uint32_t grid, uint32_t threads, size_t lds,
-                        hipStream_t st, const Args& a, hipEvent_t e0, hipEvent_t e1) {
+                        hipStream_t st, const Args& a, hipEvent_t start, hipEvent_t stop) {
   void* args[] = {const_cast<Args*>(&a)};
-  if (e0 || e1)
-    return hipExtLaunchKernel(fn, dim3(grid), dim3(threads), args, lds, st, e0, e1, 0);
+  if (start) {
+    const hipError_t e = hipEventRecord(start, st);
+    if (e != hipSuccess) return e;
+  }
+  if (stop)
+    return hipExtLaunchKernel(fn, dim3(grid), dim3(threads), args, lds, st, nullptr, stop, 0);
   return hipLaunchKernel(fn, dim3(grid), dim3(threads), args, lds, st);
 }
 
 // Launches the cell's kernel; the wave records go to `rec`, which holds at
 // least the cell's waves.
 hipError_t enqueue(const Prepared& p, hipStream_t st, sweep_wave_rec_t* rec,
-                   uint32_t* lane_out, hipEvent_t e0, hipEvent_t e1) {
+                   uint32_t* lane_out, hipEvent_t start, hipEvent_t stop) {
   if (p.c.kind == SWEEP_KIND_PLAIN) {
     const PlainArgs a{static_cast<const uint8_t*>(p.c.buf), p.plan.pub.n_vec, p.plan.pub.Q,
                       p.plan.stride, rec, lane_out, p.plan.G, (uint32_t)p.c.order,
                       p.plan.gstep, p.plan.jstep};
-    return launch_timed(p.fn, p.grid, p.threads, p.lds, st, a, e0, e1);
+    return launch_timed(p.fn, p.grid, p.threads, p.lds, st, a, start, stop);
   }
   const LdsArgs a{static_cast<const uint8_t*>(p.c.buf), p.plan.pub.n_vec, p.plan.pub.Q,
                   p.plan.stride, rec, lane_out, p.plan.wg_waves};
-  return launch_timed(p.fn, p.grid, p.threads, p.lds, st, a, e0, e1);
+  return launch_timed(p.fn, p.grid, p.threads, p.lds, st, a, start, stop);
 }
 
 std::vector<uint64_t> record_offsets(const std::vector<Prepared>& ps) {
@@ -395,19 +410,19 @@ int run_prepared(Dev& d, std::vector<Prepared>& ps, hipStream_t st,
   const std::vector<uint64_t> offs = record_offsets(ps);
   if (!wave_out) SW_TRY(ensure_dev(d.rec, d.rec_cap, offs[n]));
   SW_TRY(ensure_host(d.res_h, d.res_h_cap, n));
-  SW_TRY(ensure_events(d, 2 * n + 1));
+  SW_TRY(ensure_events(d, n + 1));
   sweep_wave_rec_t* rec = wave_out ? wave_out : d.rec;
   if (wave_out && n != 1) return fail(SWEEP_EINVAL, "wave_out takes a single cell");
   FinishArgs fin;
   SW_TRY(finish_args(d, rec, offs, &fin));
   for (size_t i = 0; i < n; ++i)
-    HIP_TRY(enqueue(ps[i], st, rec + offs[i], lane_out, d.ev[2 * i], d.ev[2 * i + 1]));
+    HIP_TRY(enqueue(ps[i], st, rec + offs[i], lane_out, i == 0 ? d.start : nullptr, d.ev[i]));
   HIP_TRY(launch_finish_cells(fin, (uint32_t)n, st));
-  HIP_TRY(hipEventRecord(d.ev[2 * n], st));
-  HIP_TRY(hipEventSynchronize(d.ev[2 * n]));
+  HIP_TRY(hipEventRecord(d.ev[n], st));
+  HIP_TRY(hipEventSynchronize(d.ev[n]));
   for (size_t i = 0; i < n; ++i) {
     float ms = 0;
-    HIP_TRY(hipEventElapsedTime(&ms, d.ev[2 * i], d.ev[2 * i + 1]));
+    HIP_TRY(hipEventElapsedTime(&ms, i == 0 ? d.start : d.ev[i - 1], d.ev[i]));
     fill_result(d, ps[i], d.res_h[i], ms, &results[i]);
   }
   return SWEEP_OK;
@@ -480,15 +495,15 @@ int xcd_run(Dev& d, const sweep_opts_t* opt, Prepared& p, uint64_t n_act, Args& 
   sweep_wave_rec_t* wave_out = opt ? opt->wave_out : nullptr;
   if (!wave_out) SW_TRY(ensure_dev(d.rec, d.rec_cap, n_act));
   a.rec = wave_out ? wave_out : d.rec;
-  SW_TRY(ensure_events(d, 3));
+  SW_TRY(ensure_events(d, 2));
   hipStream_t st = as_stream(opt);
   FinishArgs fin;
   SW_TRY(finish_args(d, a.rec, {0ull, n_act}, &fin));
   HIP_TRY(launch_clear_records(a.rec, n_act, st));
-  HIP_TRY(launch_timed(p.fn, p.grid, p.threads, p.lds, st, a, d.ev[0], d.ev[1]));
+  HIP_TRY(launch_timed(p.fn, p.grid, p.threads, p.lds, st, a, d.start, d.ev[0]));
   HIP_TRY(launch_finish_cells(fin, 1, st));
-  HIP_TRY(hipEventRecord(d.ev[2], st));
-  HIP_TRY(hipEventSynchronize(d.ev[2]));
+  HIP_TRY(hipEventRecord(d.ev[1], st));
+  HIP_TRY(hipEventSynchronize(d.ev[1]));
   std::vector<sweep_wave_rec_t> h(n_act);
   HIP_TRY(hipMemcpy(h.data(), a.rec, n_act * sizeof(sweep_wave_rec_t), hipMemcpyDeviceToHost));
   for (uint64_t i = 0; i < n_act; ++i)
@@ -499,7 +514,7 @@ int xcd_run(Dev& d, const sweep_opts_t* opt, Prepared& p, uint64_t n_act, Args& 
                                                         ", not " + std::to_string(want[i])) +
                                     ": workgroups were not dealt one per XCD per round of eight");
   float ms = 0;
-  HIP_TRY(hipEventElapsedTime(&ms, d.ev[0], d.ev[1]));
+  HIP_TRY(hipEventElapsedTime(&ms, d.start, d.ev[0]));
   fill_result(d, p, d.res_h[0], ms, out);
   return SWEEP_OK;
 }
@@ -590,19 +605,19 @@ int two_stream_impl(const void* buf, size_t bytes, int depth, int waves_plain,
   const uint32_t wa = wg_a * a.waves_a, wb = wg_b * a.waves_b;
   SW_TRY(check_outputs(opt, (uint64_t)wa + wb));
   SW_TRY(ensure_dev(d->rec, d->rec_cap, (size_t)wa + wb));
-  SW_TRY(ensure_events(*d, 3));
+  SW_TRY(ensure_events(*d, 2));
   sweep_wave_rec_t* rec = (opt && opt->wave_out) ? opt->wave_out : d->rec;
   a.rec = rec;
   a.lane_out = opt ? opt->lane_out : nullptr;
   hipStream_t st = as_stream(opt);
   FinishArgs fin;
   SW_TRY(finish_args(*d, rec, {0ull, (uint64_t)wa, (uint64_t)wa + wb}, &fin));
-  HIP_TRY(launch_timed(fn, grid, threads, lds, st, a, d->ev[0], d->ev[1]));
+  HIP_TRY(launch_timed(fn, grid, threads, lds, st, a, d->start, d->ev[0]));
   HIP_TRY(launch_finish_cells(fin, 2, st));
-  HIP_TRY(hipEventRecord(d->ev[2], st));
-  HIP_TRY(hipEventSynchronize(d->ev[2]));
+  HIP_TRY(hipEventRecord(d->ev[1], st));
+  HIP_TRY(hipEventSynchronize(d->ev[1]));
   float ms = 0;
-  HIP_TRY(hipEventElapsedTime(&ms, d->ev[0], d->ev[1]));
+  HIP_TRY(hipEventElapsedTime(&ms, d->start, d->ev[0]));
   for (int s = 0; s < 2; ++s) {
     const bool on = s == 0 ? waves_plain > 0 : waves_async > 0;
     Prepared p;
@@ -1186,22 +1201,22 @@ int sweep_reduce_fp(const void* payload, size_t n_elems, int dtype,
   HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fn, 256, 0));
   SW_TRY(ensure_dev(d->rec, d->rec_cap, (size_t)grid * 4));
   SW_TRY(ensure_dev(d->partials, d->partials_cap, (size_t)grid * 2));
-  SW_TRY(ensure_events(*d, 3));
+  SW_TRY(ensure_events(*d, 2));
   a.partials = d->partials;
   a.rec = d->rec;
   hipStream_t st = as_stream(opt);
   FinishArgs fin;
   SW_TRY(finish_args(*d, d->rec, {0ull, (uint64_t)grid * 4}, &fin));
-  HIP_TRY(launch_timed(fn, grid, 256u, 0, st, a, d->ev[0], d->ev[1]));
+  HIP_TRY(launch_timed(fn, grid, 256u, 0, st, a, d->start, d->ev[0]));
   HIP_TRY(launch_reduce_finish(d->partials, grid, d->dsum, st));
   HIP_TRY(launch_finish_cells(fin, 1, st));
   HIP_TRY(hipMemcpyAsync(d->dsum_h, d->dsum, sizeof(double), hipMemcpyDeviceToHost, st));
-  HIP_TRY(hipEventRecord(d->ev[2], st));
-  HIP_TRY(hipEventSynchronize(d->ev[2]));
+  HIP_TRY(hipEventRecord(d->ev[1], st));
+  HIP_TRY(hipEventSynchronize(d->ev[1]));
   *sum = *d->dsum_h;
   if (out) {
     float ms = 0;
-    HIP_TRY(hipEventElapsedTime(&ms, d->ev[0], d->ev[1]));
+    HIP_TRY(hipEventElapsedTime(&ms, d->start, d->ev[0]));
     Prepared p;
     p.c.total_logical_loads = a.n_vec;
     p.grid = grid;
