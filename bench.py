@@ -44,6 +44,7 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 PLAIN_SOURCES = ["paper_2608_15764_amd/csrc/kernels_plain.hip",
+                 "paper_2608_15764_amd/csrc/seg_walk.hpp",
                  "paper_2608_15764_amd/csrc/device.hpp"]
 PMC_SUMMARY = os.path.join(ROOT, "profiles", "plain_kload_1GiB_ksweep_pmc.txt")
 HBM_PEAK_GBPS = 8000.0

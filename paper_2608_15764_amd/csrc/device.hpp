@@ -83,15 +83,19 @@ __device__ __forceinline__ void fold(uint32_t w, uint32_t& s, uint32_t& x) {
   s += w;
   x ^= w;
 }
+// a ^ b ^ c in one instruction (gfx950's three-operand truth table)
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+  return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
+}
 __device__ __forceinline__ void fold(u32x2 w, uint32_t& s, uint32_t& x) {
-  fold(w.x, s, x);
-  fold(w.y, s, x);
+  s += w.x + w.y;
+  x = xor3(x, w.x, w.y);
 }
 __device__ __forceinline__ void fold(u32x4 w, uint32_t& s, uint32_t& x) {
-  fold(w.x, s, x);
-  fold(w.y, s, x);
-  fold(w.z, s, x);
-  fold(w.w, s, x);
+  s += w.x + w.y;
+  x = xor3(x, w.x, w.y);
+  s += w.z + w.w;
+  x = xor3(x, w.z, w.w);
 }
 
 // ------------------------------------------------------- wave reductions

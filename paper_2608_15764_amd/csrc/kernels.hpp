@@ -14,25 +14,30 @@ constexpr int kMaxK = 16;
 constexpr int kPlainWgThreads = 256;   // 4 waves, one per SIMD
 
 // Plain K-load cell.  Round robin (and strided): wave w of n_waves handles
-// wave-groups q = w, w + n_waves, ... below Q; blocked: q = w*G .. w*G +
-// G - 1.  Load j of group q reads the 64 vectors starting at vector
-// (q*gstep + j*jstep) mod n_vec: gstep = K*64, jstep = 64 (adjacent
-// segments, (q*K + j)*64), or in the strided layout gstep = 64, jstep =
-// Q*64 ((j*Q + q)*64).  `stride` is the vector step between a wave's
-// consecutive groups, mod n_vec: n_waves*gstep (round robin, strided) or
-// gstep (blocked).
+// wave-groups q = w, w + n_waves, ... below Q, iters of them and one more if
+// w < extra; blocked: q = w*G .. w*G + G - 1.  All steps are in bytes: load j
+// of group q reads the 64 vectors starting at (q*gstep + j*jstep) mod bytes:
+// gstep = K segments, jstep = 1 (adjacent segments, (q*K + j) segments), or
+// in the strided layout gstep = 1 segment, jstep = Q segments ((j*Q + q)
+// segments).  `stride` is the step between a wave's consecutive groups, mod
+// bytes: n_waves*gstep (round robin, strided) or gstep (blocked).
 struct PlainArgs {
   const uint8_t* buf;
-  uint64_t n_vec;
+  uint64_t bytes;
   uint64_t Q;
   uint64_t stride;
   sweep_wave_rec_t* rec;
   uint32_t* lane_out;
   uint64_t G;          // groups per wave in blocked order
   uint32_t order;      // SWEEP_ORDER_*
-  uint64_t gstep;      // start vector of group q: q * gstep (mod n_vec)
-  uint64_t jstep;      // from load j to load j + 1 (mod n_vec), below n_vec
+  uint32_t iters;      // Q / n_waves
+  uint32_t extra;      // Q mod n_waves
+  uint64_t gstep;
+  uint64_t jstep;      // mod bytes
 };
+
+// Buffers of this many bytes and more are walked with 64-bit cursors.
+constexpr uint64_t kFarBytes = 1ull << 32;
 
 // Fused batch of plain cells that share K, vector width, cache policy and
 // launch shape: one persistent launch over their concatenated wave-groups.
@@ -180,8 +185,8 @@ hipError_t static_scratch(int ordinal, uint8_t** ptr);
 // ---- kernel lookup: the host launches these with their one argument
 // struct (PlainArgs, LdsArgs, TwoStreamArgs, ReduceArgs); nullptr for an
 // unknown combination.
-// plain (kernels_plain.hip)
-const void* plain_kernel(int K, int V, int policy);
+// plain (kernels_plain.hip); `far` for buffers of kFarBytes and more
+const void* plain_kernel(int K, int V, int policy, bool far);
 // fused plain batch (kernels_fused.hip)
 const void* fused_kernel(int K, int V, int policy);
 const void* xcd_kernel(int policy);

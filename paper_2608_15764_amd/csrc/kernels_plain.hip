@@ -12,47 +12,74 @@
 
 #include "device.hpp"
 #include "kernels.hpp"
+#include "seg_walk.hpp"
 
 namespace ilp {
 
-template <int K, int V, int POL>
-__global__ __launch_bounds__(kPlainWgThreads) void plain_kload(PlainArgs a) {
+template <int K, int V, int POL, template <int, int> class Walk>
+__device__ __forceinline__ void plain_cell(const PlainArgs& a) {
   const uint64_t t0 = wall_ticks();
   const uint32_t lane = lane_id();
   const uint32_t wid = blockIdx.x * (kPlainWgThreads / kWave) + wave_in_wg();
-  const uint32_t n_waves = gridDim.x * (kPlainWgThreads / kWave);
 
-  uint32_t s = 0, x = 0;
-  // this wave's groups: [q0, q1) in steps of qs (wave-uniform scalars)
-  uint64_t q0 = wid, q1 = a.Q, qs = n_waves;
+  // Sinks of even and odd loads.  Two chains are no faster than one; they
+  // keep the cells that do not reach 8 waves per SIMD what they were, K = 15
+  // and 16 with 16-byte loads (66 and 70 registers; one chain would need 64).
+  uint32_t s = 0, x = 0, s1 = 0, x1 = 0;
+  // this wave's first group and their number (wave-uniform scalars)
+  uint64_t q0 = wid;
+  uint32_t iters = a.iters + (wid < a.extra ? 1u : 0u);
   if (a.order == SWEEP_ORDER_BLOCKED) {
     q0 = (uint64_t)wid * a.G;
-    q1 = q0 + a.G < a.Q ? q0 + a.G : a.Q;
-    qs = 1;
+    const uint64_t left = q0 < a.Q ? a.Q - q0 : 0;
+    iters = (uint32_t)(left < a.G ? left : a.G);
   }
-  // start vector of the first group, advanced by `stride` per iteration,
-  // both modulo the buffer's vector count
-  uint64_t p = (q0 * a.gstep) % a.n_vec;
+  if (iters) {
+    typedef Walk<V, POL> W;
+    const W walk(a.buf, a.bytes, lane);
+    const typename W::Step next_load = walk.step(a.jstep, a.bytes);
+    const typename W::Step next_group = walk.step(a.stride, a.bytes);
+    // the first group's start; most lie inside the buffer
+    uint64_t off = q0 * a.gstep;
+    if (off >= a.bytes) off %= a.bytes;
+    typename W::Cursor p = walk.at(off);
 #pragma unroll 1
-  for (uint64_t q = q0; q < q1; q += qs) {
-    typename Vec<V>::T v[K];
-    uint64_t pj = p;
+    for (; iters; --iters) {
+      typename Vec<V>::T v[K];
+      typename W::Cursor pj = p;
+      const uint32_t lo = walk.lane_offset();
 #pragma unroll
-    for (int j = 0; j < K; ++j) {
-      v[j] = load_seg<V, POL>(a.buf + pj * V, lane);
-      pj += a.jstep;
-      if (pj >= a.n_vec) pj -= a.n_vec;
+      for (int j = 0; j < K; ++j) {
+        v[j] = walk.load(pj, lo);
+        __builtin_amdgcn_sched_barrier(0);   // not all the stepping first
+        pj = next_load(pj);
+      }
+      // all K loads are issued before the first is consumed: without this
+      // barrier the scheduler may refill registers early to raise occupancy
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int j = 0; j < K; ++j) {
+        if (j & 1) fold(v[j], s1, x1);
+        else fold(v[j], s, x);
+      }
+      p = next_group(p);
     }
-    // all K loads are issued before the first is consumed: without this
-    // barrier the scheduler may refill registers early to raise occupancy
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int j = 0; j < K; ++j) fold(v[j], s, x);
-    p += a.stride;
-    if (p >= a.n_vec) p -= a.n_vec;
+    s += s1;
+    x ^= x1;
   }
   const uint64_t t1 = wall_ticks();
   wave_epilogue(s, x, t0, t1, wid, a.rec, a.lane_out);
+}
+
+template <int K, int V, int POL>
+__global__ __launch_bounds__(kPlainWgThreads) void plain_kload(PlainArgs a) {
+  plain_cell<K, V, POL, NearWalk>(a);
+}
+
+// The same cell over 4 GiB and more.
+template <int K, int V, int POL>
+__global__ __launch_bounds__(kPlainWgThreads) void plain_kload_far(PlainArgs a) {
+  plain_cell<K, V, POL, FarWalk>(a);
 }
 
 namespace {
@@ -60,16 +87,16 @@ namespace {
 typedef void (*PlainFn)(PlainArgs);
 
 template <int V, int POL, int... Ks>
-constexpr std::array<PlainFn, sizeof...(Ks)> row(std::integer_sequence<int, Ks...>) {
-  return {&plain_kload<Ks + 1, V, POL>...};
+constexpr std::array<PlainFn, 2 * sizeof...(Ks)> row(std::integer_sequence<int, Ks...>) {
+  return {&plain_kload<Ks + 1, V, POL>..., &plain_kload_far<Ks + 1, V, POL>...};
 }
 
 template <int V, int POL>
 constexpr auto kRow = row<V, POL>(std::make_integer_sequence<int, kMaxK>{});
 
-// [vector width index][policy][K-1]
+// [vector width index][policy][far * kMaxK + K-1]
 const PlainFn* table(int vi, int pol) {
-  static const std::array<PlainFn, kMaxK> t[3][kNumPolicies] = {
+  static const std::array<PlainFn, 2 * kMaxK> t[3][kNumPolicies] = {
       {kRow<4, 0>, kRow<4, 1>, kRow<4, 2>, kRow<4, 3>},
       {kRow<8, 0>, kRow<8, 1>, kRow<8, 2>, kRow<8, 3>},
       {kRow<16, 0>, kRow<16, 1>, kRow<16, 2>, kRow<16, 3>},
@@ -81,10 +108,10 @@ int width_index(int V) { return V == 4 ? 0 : V == 8 ? 1 : V == 16 ? 2 : -1; }
 
 }  // namespace
 
-const void* plain_kernel(int K, int V, int policy) {
+const void* plain_kernel(int K, int V, int policy, bool far) {
   const int vi = width_index(V);
   if (vi < 0 || K < 1 || K > kMaxK || policy < 0 || policy >= kNumPolicies) return nullptr;
-  return reinterpret_cast<const void*>(table(vi, policy)[K - 1]);
+  return reinterpret_cast<const void*>(table(vi, policy)[(far ? kMaxK : 0) + K - 1]);
 }
 
 }  // namespace ilp

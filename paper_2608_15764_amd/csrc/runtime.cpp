@@ -241,7 +241,8 @@ int prepare(Dev& d, const sweep_cell_t& c, int pin, Prepared* out, bool cache = 
     return fail(SWEEP_EALIGN, "buffer must be 16-byte aligned");
   if (c.cache_policy < 0 || c.cache_policy > 3)
     return fail(SWEEP_EINVAL, "unknown cache policy");
-  p.fn = c.kind == SWEEP_KIND_PLAIN ? plain_kernel(c.K, c.vec_width, c.cache_policy)
+  p.fn = c.kind == SWEEP_KIND_PLAIN ? plain_kernel(c.K, c.vec_width, c.cache_policy,
+                                                        c.bytes >= kFarBytes)
                                     : lds_kernel(c.kind, c.K, c.cache_policy);
   if (!p.fn) return fail(SWEEP_EINVAL, "no kernel for this cell");
   p.grid = p.plan.pub.grid_wgs;
@@ -302,9 +303,21 @@ hipError_t launch_timed(const void* fn, uint32_t grid, uint32_t threads, size_t 
 hipError_t enqueue(const Prepared& p, hipStream_t st, sweep_wave_rec_t* rec,
                    uint32_t* lane_out, hipEvent_t start, hipEvent_t stop) {
   if (p.c.kind == SWEEP_KIND_PLAIN) {
-    const PlainArgs a{static_cast<const uint8_t*>(p.c.buf), p.plan.pub.n_vec, p.plan.pub.Q,
-                      p.plan.stride, rec, lane_out, p.plan.G, (uint32_t)p.c.order,
-                      p.plan.gstep, p.plan.jstep};
+    const sweep_plan_t& o = p.plan.pub;
+    const uint64_t V = (uint64_t)p.c.vec_width;
+    PlainArgs a;
+    a.buf = static_cast<const uint8_t*>(p.c.buf);
+    a.bytes = o.n_vec * V;
+    a.Q = o.Q;
+    a.stride = p.plan.stride * V;
+    a.rec = rec;
+    a.lane_out = lane_out;
+    a.G = p.plan.G;
+    a.order = (uint32_t)p.c.order;
+    a.iters = (uint32_t)(o.Q / o.waves);
+    a.extra = (uint32_t)(o.Q % o.waves);
+    a.gstep = p.plan.gstep * V;
+    a.jstep = p.plan.jstep * V;
     return launch_timed(p.fn, p.grid, p.threads, p.lds, st, a, start, stop);
   }
   const LdsArgs a{static_cast<const uint8_t*>(p.c.buf), p.plan.pub.n_vec, p.plan.pub.Q,

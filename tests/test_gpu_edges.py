@@ -64,3 +64,37 @@ def test_cells_of_one_call_keep_apart(n):
         assert (a["sum32"], a["xor32"]) == (b["sum32"], b["xor32"]) == (one["sum32"],
                                                                        one["xor32"])
         assert a["window_ticks"] > 0 and b["window_ticks"] > 0
+
+
+def _prefix_sinks(words, n):
+    """(sum32, xor32) of the first n of `words` (a device int32 tensor)."""
+    s, x = int(words[:n].sum(dtype=torch.int64)) & 0xFFFFFFFF, 0
+    part = words[:n]
+    while part.numel() > 1024:
+        half = part.numel() // 2
+        part = torch.cat((part[:half] ^ part[half:2 * half], part[2 * half:]))
+    for w in part.tolist():
+        x ^= w & 0xFFFFFFFF
+    return s, x
+
+
+@pytest.mark.parametrize("order", [0, 1, 2])
+@pytest.mark.parametrize("policy", [0, 1, 2, 3])
+@pytest.mark.parametrize("nbytes", [(1 << 31) - 3072, (1 << 31) + 3072, (1 << 32) - 3072, 1 << 32,
+                                    (1 << 32) + 3072])
+def test_plain_at_the_32_bit_edges(nbytes, policy, order):
+    """Buffers around 2 and 4 GiB, where byte offsets fill 31 and 32 bits
+    and the 64-bit walk takes over; a pass and a bit, so that groups wrap."""
+    buf = dev_bytes(nbytes)
+    isw.sweep_fill_u32(buf, nbytes, SEED + 3)
+    n_vec, K = nbytes // 16, 5
+    L = n_vec + 64 * 1000 + 77
+    print("plain", nbytes, "policy", policy, "order", order, flush=True)
+    r = isw.sweep_plain(buf, nbytes, K, 16, 16, L,
+                        isw.make_opts(cache_policy=policy, order=order))
+    issued = 64 * K * (L // (64 * K))
+    words = buf.view(torch.int32)
+    s, x = _prefix_sinks(words, nbytes // 4)
+    more, morex = _prefix_sinks(words, (issued - n_vec) * 4)
+    assert r["issued_loads"] == issued
+    assert (r["sum32"], r["xor32"]) == ((s + more) & 0xFFFFFFFF, x ^ morex)

@@ -260,3 +260,20 @@ def test_xcd_subset_loop_is_the_plain_K8_loop(P, kernel):
     waits = [i for i, l in enumerate(body) if l.startswith("s_waitcnt") and "vmcnt" in l]
     assert waits and waits[0] > loads[-1]
     assert not any(l.startswith(("global_store", "buffer_store", "scratch_")) for l in body)
+
+
+@pytest.mark.parametrize("P", [0, 3])
+@pytest.mark.parametrize("V", [4, 16])
+@pytest.mark.parametrize("K", [1, 7, 16])
+@pytest.mark.parametrize("kernel", ["plain_kload", "plain_kload_far"])
+def test_plain_walks_step_in_scalar_registers(plain, kernel, K, V, P):
+    """Both walks of the plain loop (below and from 4 GiB) keep K loads before
+    the first wait and step from load to load without vector compares or
+    64-bit vector address arithmetic."""
+    text, funcs = plain
+    name = f"_ZN3ilp{len(kernel)}{kernel}ILi{K}ELi{V}ELi{P}EEEvNS_9PlainArgsE"
+    body = _loop(funcs[name])
+    loads = [i for i, l in enumerate(body) if LOAD.match(l)]
+    waits = [i for i, l in enumerate(body) if l.startswith("s_waitcnt") and "vmcnt" in l]
+    assert len(loads) == K and waits[0] > loads[-1], name
+    assert not any(l.startswith(("v_cmp", "v_lshl_add_u64", "flat_")) for l in body), name
