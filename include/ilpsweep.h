@@ -305,7 +305,7 @@ int sweep_plain_noalloc(const void* buf, size_t bytes, int K, int vec_width,
  * ring of `depth` 1 KiB LDS slots; each slot is filled by one
  * global_load_lds_dwordx4 (16 bytes per lane), waited for with
  * s_waitcnt vmcnt(depth - 1), read back by its own lane (ds_read_b128),
- * folded, and refilled, so `depth` requests stay in flight.  The address
+ * refilled and folded, so `depth` requests stay in flight.  The address
  * map is the plain map with K = depth, so the sinks equal sweep_plain's.
  *   depth         1..16
  *   vec_width     16

@@ -62,25 +62,28 @@ struct FusedArgs {
   sweep_wave_rec_t* rec;   // n_pts * n_waves records
 };
 
-// LDS-ring cell (async or matched), `waves` waves per workgroup.
+// LDS-ring cell (async or matched), `waves` waves per workgroup; steps and
+// iteration counts as in PlainArgs, round robin.
 struct LdsArgs {
   const uint8_t* buf;
-  uint64_t n_vec;
-  uint64_t Q;
-  uint64_t stride;        // (n_waves*D*64) mod n_vec
+  uint64_t bytes;
+  uint64_t stride;        // n_waves groups of D segments, mod bytes
   sweep_wave_rec_t* rec;
   uint32_t* lane_out;
+  uint32_t iters, extra;
   uint32_t waves;         // waves per workgroup
 };
 
 // Two co-resident streams: A (plain K = D) on region A, B (LDS-async ring
 // of depth D) on region B.  Records of A come first (n_waves_a of them),
 // then those of B.
+struct StreamArgs {
+  const uint8_t* buf;
+  uint64_t bytes, stride;
+  uint32_t iters, extra;
+};
 struct TwoStreamArgs {
-  const uint8_t* buf_a;
-  uint64_t n_vec_a, Q_a, stride_a;
-  const uint8_t* buf_b;
-  uint64_t n_vec_b, Q_b, stride_b;
+  StreamArgs a, b;
   sweep_wave_rec_t* rec;   // n_waves_a + n_waves_b records
   uint32_t* lane_out;      // lanes of A then lanes of B, or null
   uint32_t waves_a, waves_b;  // per workgroup
@@ -196,8 +199,8 @@ const void* xcd_split_kernel(int policy);
 hipError_t launch_clear_records(sweep_wave_rec_t* rec, uint64_t n, hipStream_t st);
 
 // ---- LDS paths (kernels_lds.hip)
-const void* lds_kernel(int kind, int D, int policy);
-const void* two_stream_kernel(int D, int policy);
+const void* lds_kernel(int kind, int D, int policy, bool far);
+const void* two_stream_kernel(int D, int policy, bool far);
 
 // ---- pointer chase (kernels_chase.hip)
 const void* chase_kernel(int policy);

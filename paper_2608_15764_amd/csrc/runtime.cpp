@@ -241,9 +241,9 @@ int prepare(Dev& d, const sweep_cell_t& c, int pin, Prepared* out, bool cache = 
     return fail(SWEEP_EALIGN, "buffer must be 16-byte aligned");
   if (c.cache_policy < 0 || c.cache_policy > 3)
     return fail(SWEEP_EINVAL, "unknown cache policy");
-  p.fn = c.kind == SWEEP_KIND_PLAIN ? plain_kernel(c.K, c.vec_width, c.cache_policy,
-                                                        c.bytes >= kFarBytes)
-                                    : lds_kernel(c.kind, c.K, c.cache_policy);
+  const bool far = c.bytes >= kFarBytes;
+  p.fn = c.kind == SWEEP_KIND_PLAIN ? plain_kernel(c.K, c.vec_width, c.cache_policy, far)
+                                    : lds_kernel(c.kind, c.K, c.cache_policy, far);
   if (!p.fn) return fail(SWEEP_EINVAL, "no kernel for this cell");
   p.grid = p.plan.pub.grid_wgs;
   p.threads = p.plan.pub.wg_threads;
@@ -302,9 +302,9 @@ hipError_t launch_timed(const void* fn, uint32_t grid, uint32_t threads, size_t 
 // least the cell's waves.
 hipError_t enqueue(const Prepared& p, hipStream_t st, sweep_wave_rec_t* rec,
                    uint32_t* lane_out, hipEvent_t start, hipEvent_t stop) {
+  const sweep_plan_t& o = p.plan.pub;
+  const uint64_t V = (uint64_t)p.c.vec_width;
   if (p.c.kind == SWEEP_KIND_PLAIN) {
-    const sweep_plan_t& o = p.plan.pub;
-    const uint64_t V = (uint64_t)p.c.vec_width;
     PlainArgs a;
     a.buf = static_cast<const uint8_t*>(p.c.buf);
     a.bytes = o.n_vec * V;
@@ -320,8 +320,15 @@ hipError_t enqueue(const Prepared& p, hipStream_t st, sweep_wave_rec_t* rec,
     a.jstep = p.plan.jstep * V;
     return launch_timed(p.fn, p.grid, p.threads, p.lds, st, a, start, stop);
   }
-  const LdsArgs a{static_cast<const uint8_t*>(p.c.buf), p.plan.pub.n_vec, p.plan.pub.Q,
-                  p.plan.stride, rec, lane_out, p.plan.wg_waves};
+  LdsArgs a;
+  a.buf = static_cast<const uint8_t*>(p.c.buf);
+  a.bytes = o.n_vec * V;
+  a.stride = p.plan.stride * V;
+  a.rec = rec;
+  a.lane_out = lane_out;
+  a.iters = (uint32_t)(o.Q / o.waves);
+  a.extra = (uint32_t)(o.Q % o.waves);
+  a.waves = p.plan.wg_waves;
   return launch_timed(p.fn, p.grid, p.threads, p.lds, st, a, start, stop);
 }
 
@@ -585,30 +592,33 @@ int two_stream_impl(const void* buf, size_t bytes, int depth, int waves_plain,
   const uint64_t La = total_logical_loads / 2, Lb = total_logical_loads - La;
   TwoStreamArgs a;
   std::memset(&a, 0, sizeof(a));
-  a.buf_a = static_cast<const uint8_t*>(buf);
-  a.n_vec_a = half;
-  a.buf_b = static_cast<const uint8_t*>(buf) + half * 16;
-  a.n_vec_b = n_vec - half;
   a.waves_a = (uint32_t)waves_plain;
   a.waves_b = (uint32_t)waves_async;
   a.b_plain = b_plain ? 1u : 0u;
   a.split = split ? 1u : 0u;
-  if (waves_plain) region_plan(a.n_vec_a, depth, La, wg_a * a.waves_a, &a.Q_a, &a.stride_a);
-  if (waves_async) region_plan(a.n_vec_b, depth, Lb, wg_b * a.waves_b, &a.Q_b, &a.stride_b);
-  if ((waves_plain && a.Q_a == 0) || (waves_async && a.Q_b == 0))
+  // waves and wave-groups of each stream
+  const uint64_t nwa = (uint64_t)wg_a * a.waves_a, nwb = (uint64_t)wg_b * a.waves_b;
+  uint64_t Qa = 0, Qb = 0, stride_a = 0, stride_b = 0;
+  if (waves_plain) region_plan(half, depth, La, (uint32_t)nwa, &Qa, &stride_a);
+  if (waves_async) region_plan(n_vec - half, depth, Lb, (uint32_t)nwb, &Qb, &stride_b);
+  if ((waves_plain && Qa == 0) || (waves_async && Qb == 0))
     return fail(SWEEP_EINVAL, "L is smaller than one wave-group per stream");
   // per-wave iteration counts are reported in 32 bits
-  const uint64_t nwa = (uint64_t)wg_a * a.waves_a, nwb = (uint64_t)wg_b * a.waves_b;
-  if ((nwa && (a.Q_a + nwa - 1) / nwa > UINT32_MAX) ||
-      (nwb && (a.Q_b + nwb - 1) / nwb > UINT32_MAX))
+  if ((nwa && (Qa + nwa - 1) / nwa > UINT32_MAX) || (nwb && (Qb + nwb - 1) / nwb > UINT32_MAX))
     return fail(SWEEP_EINVAL, "a wave would run more than 2^32 - 1 iterations");
+  auto stream = [](const uint8_t* p, uint64_t vecs, uint64_t stride, uint64_t Q, uint64_t nw) {
+    return StreamArgs{p, vecs * 16, stride * 16, nw ? (uint32_t)(Q / nw) : 0u,
+                      nw ? (uint32_t)(Q % nw) : 0u};
+  };
+  a.a = stream(static_cast<const uint8_t*>(buf), half, stride_a, Qa, nwa);
+  a.b = stream(static_cast<const uint8_t*>(buf) + half * 16, n_vec - half, stride_b, Qb, nwb);
   const uint32_t threads =
       (uint32_t)(split ? std::max(waves_plain, waves_async) : waves_plain + waves_async) * 64u;
   const uint32_t ring = b_plain ? 0u : (uint32_t)waves_async * (uint32_t)depth * 1024u;
   if (ring > d->lds_per_wg_max) return fail(SWEEP_EOCCUPANCY, "LDS ring exceeds the per-workgroup LDS");
   size_t lds = ring;
   if (pin_of(opt)) lds = std::max<size_t>(lds, pin_padding(1, ring, d->lds_per_cu, d->lds_per_wg_max));
-  const void* fn = two_stream_kernel(depth, pol);
+  const void* fn = two_stream_kernel(depth, pol, (n_vec - half) * 16 >= kFarBytes);
   if (!fn) return fail(SWEEP_EINVAL, "no two-stream kernel for this depth and policy");
   hipFuncAttributes fa;
   HIP_TRY(hipFuncGetAttributes(&fa, fn));
@@ -642,12 +652,12 @@ int two_stream_impl(const void* buf, size_t bytes, int depth, int waves_plain,
     p.lds = lds;
     p.max_wgs = nb;
     p.fa = fa;
-    const uint64_t Q = s == 0 ? a.Q_a : a.Q_b;
+    const uint64_t Q = s == 0 ? Qa : Qb;
     const uint32_t nw = s == 0 ? wa : wb;
     p.plan.pub.grid_wgs = grid;
     p.plan.pub.wg_threads = threads;
     p.plan.pub.waves = nw;
-    p.plan.pub.n_vec = s == 0 ? a.n_vec_a : a.n_vec_b;
+    p.plan.pub.n_vec = s == 0 ? half : n_vec - half;
     p.plan.pub.Q = Q;
     p.plan.pub.issued_loads = 64ull * (uint64_t)depth * Q;
     p.plan.pub.issued_bytes = p.plan.pub.issued_loads * 16ull;

@@ -86,6 +86,13 @@ struct NearWalk {
     if constexpr (kBuffer) return load_buffer<V, POL>(r, lo, c);
     else return load_global<V, POL>(base + c, lo);
   }
+  // for LDS-direct requests, which are global loads under every policy
+  __device__ __forceinline__ uint64_t address(Cursor c) const { return base + c; }
+  __device__ __forceinline__ uint32_t lds_lane_offset() const {
+    uint32_t o = lane_off;
+    asm volatile("" : "+v"(o));
+    return o;
+  }
 };
 
 // The cursor is offset - n, in [-n, 0).
@@ -127,6 +134,12 @@ struct FarWalk {
     } else {
       return load_global<V, POL>(seg, lo);
     }
+  }
+  __device__ __forceinline__ uint64_t address(Cursor c) const { return end + (uint64_t)c; }
+  __device__ __forceinline__ uint32_t lds_lane_offset() const {
+    uint32_t o = lane * V;
+    asm volatile("" : "+v"(o));
+    return o;
   }
 };
 

@@ -2,13 +2,27 @@
 // kernel.  A wave owns wave-groups q = wid, wid + n_waves, ... below Q; the
 // request for load j of group q is the 64-lane segment starting at vector
 // (q*D + j)*64 mod n_vec, exactly the plain map with K = D.
+//
+// At one or two waves per CU these loops are bound by a wave's own
+// instruction stream, from a slot's arrival to its refill.  The steps between
+// requests are scalar (seg_walk.hpp), the LDS-direct ring refills a slot
+// before it folds what it read, and the scheduling barriers keep the requests
+// in the order in which the loop waits for them, so that every wait leaves
+// D - 1 in flight.  2 GiB, one wave per CU, depth 8 and 16: LDS-direct 590 ->
+// 555 and 505 -> 392 us, matched 780 -> 545 and 560 -> 437 under the default
+// policy (585 -> 537 and 462 -> 431 with sc1 nt); two streams of 4 waves on
+// different CUs at depth 4, 415 -> 349 us.  From 4 waves per CU and depth 8
+// on HBM bounds them, as before.
 #pragma once
 
 #include <utility>
 
 #include "device.hpp"
+#include "seg_walk.hpp"
 
 namespace ilp {
+
+constexpr uint64_t kSegBytes = kWave * 16;   // one 64-lane segment of 16-byte vectors
 
 template <typename F, int... Js>
 __device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, Js...>) {
@@ -20,89 +34,102 @@ __device__ __forceinline__ void static_for(F&& f) {
   static_for_impl(f, std::make_integer_sequence<int, N>{});
 }
 
-__device__ __forceinline__ uint64_t wrap_add(uint64_t p, uint64_t d, uint64_t n) {
-  p += d;
-  return p >= n ? p - n : p;
-}
+// One wave's share of a region: its groups and their addresses, in bytes.
+struct Share {
+  const uint8_t* buf;
+  uint64_t bytes;
+  uint64_t stride;      // between two of the wave's groups, mod bytes
+  uint32_t wid;
+  uint32_t iters;       // groups of this wave
+};
 
-// Number of groups of wave `wid`.
-__device__ __forceinline__ uint64_t groups_of(uint64_t wid, uint64_t Q,
-                                              uint64_t n_waves) {
-  return wid < Q ? (Q - 1 - wid) / n_waves + 1 : 0;
+// Start of the wave's first group of D segments; most lie inside the region.
+template <int D>
+__device__ __forceinline__ uint64_t first_group(const Share& a) {
+  uint64_t off = (uint64_t)a.wid * (D * kSegBytes);
+  if (off >= a.bytes) off %= a.bytes;
+  return off;
 }
 
 // One 16-byte-per-lane LDS-direct request: lane l's bytes land in
 // slot[l] (global_load_lds_dwordx4 writes LDS at M0 + 16*lane).  The last
 // builtin operand is the cache policy: 0, nt (2), sc1 (16) or sc1 nt (18).
 template <int POL>
-__device__ __forceinline__ void lds_issue(const uint8_t* seg, u32x4* slot,
-                                          uint32_t lane) {
+__device__ __forceinline__ void lds_issue(uint64_t seg, uint32_t lane_off, u32x4* slot) {
   typedef __attribute__((address_space(3))) void lds_void;
   lds_void* dst = (lds_void*)slot;
+  asm("" : "+s"(seg));
+  const GlobalBytes src = (GlobalBytes)seg + lane_off;
   if constexpr (POL == SWEEP_CACHE_DEFAULT) {
-    __builtin_amdgcn_global_load_lds(seg + lane * 16, dst, 16, 0, 0);
+    __builtin_amdgcn_global_load_lds(src, dst, 16, 0, 0);
   } else if constexpr (POL == SWEEP_CACHE_NT) {
-    __builtin_amdgcn_global_load_lds(seg + lane * 16, dst, 16, 0, 2);
+    __builtin_amdgcn_global_load_lds(src, dst, 16, 0, 2);
   } else if constexpr (POL == SWEEP_CACHE_BYPASS_L1) {
-    __builtin_amdgcn_global_load_lds(seg + lane * 16, dst, 16, 0, 16);
+    __builtin_amdgcn_global_load_lds(src, dst, 16, 0, 16);
   } else {
-    __builtin_amdgcn_global_load_lds(seg + lane * 16, dst, 16, 0, 18);
+    __builtin_amdgcn_global_load_lds(src, dst, 16, 0, 18);
   }
 }
 
 // Plain batched loop (K loads, then K folds) over one region.
-template <int K, int POL>
-__device__ __forceinline__ void plain_loop16(const uint8_t* buf, uint64_t n_vec,
-                                             uint64_t Q, uint64_t stride,
-                                             uint32_t wid, uint32_t n_waves,
-                                             uint32_t lane, uint32_t& s,
+template <int K, class W>
+__device__ __forceinline__ void plain_loop16(const Share& a, uint32_t lane, uint32_t& s,
                                              uint32_t& x) {
-  uint64_t p = ((uint64_t)wid * (K * kWave)) % n_vec;
+  if (a.iters == 0) return;
+  const W walk(a.buf, a.bytes, lane);
+  const typename W::Step next_load = walk.step(kSegBytes % a.bytes, a.bytes);
+  const typename W::Step next_group = walk.step(a.stride, a.bytes);
+  typename W::Cursor p = walk.at(first_group<K>(a));
 #pragma unroll 1
-  for (uint64_t q = wid; q < Q; q += n_waves) {
+  for (uint32_t i = a.iters; i; --i) {
     u32x4 v[K];
-    uint64_t pj = p;
+    typename W::Cursor pj = p;
+    const uint32_t lo = walk.lane_offset();
 #pragma unroll
     for (int j = 0; j < K; ++j) {
-      v[j] = load_seg<16, POL>(buf + pj * 16, lane);
-      pj = wrap_add(pj, kWave, n_vec);
+      v[j] = walk.load(pj, lo);
+      __builtin_amdgcn_sched_barrier(0);
+      pj = next_load(pj);
     }
     __builtin_amdgcn_sched_barrier(0);   // all K issued before any fold
 #pragma unroll
     for (int j = 0; j < K; ++j) fold(v[j], s, x);
-    p = wrap_add(p, stride, n_vec);
+    p = next_group(p);
   }
 }
 
-// LDS-direct ring of depth D: D requests in flight, each consumed as soon
-// as it lands (s_waitcnt vmcnt(D-1)) and its slot refilled at once.
-template <int D, int POL>
-__device__ __forceinline__ void async_ring_loop(const uint8_t* buf, uint64_t n_vec,
-                                                uint64_t Q, uint64_t stride,
-                                                uint32_t wid, uint32_t n_waves,
-                                                uint32_t lane, u32x4* ring,
+// LDS-direct ring of depth D: D requests in flight, each slot read as soon
+// as it lands (s_waitcnt vmcnt(D-1)) and refilled at once; the read words
+// are folded behind the refill, which is what the ring waits for.
+template <int D, int POL, class W>
+__device__ __forceinline__ void async_ring_loop(const Share& a, uint32_t lane, u32x4* ring,
                                                 uint32_t& s, uint32_t& x) {
-  const uint64_t iters = groups_of(wid, Q, n_waves);
-  if (iters == 0) return;
-  uint64_t p = ((uint64_t)wid * (D * kWave)) % n_vec;
+  if (a.iters == 0) return;
+  const W walk(a.buf, a.bytes, lane);
+  const typename W::Step next_load = walk.step(kSegBytes % a.bytes, a.bytes);
+  const typename W::Step next_group = walk.step(a.stride, a.bytes);
+  typename W::Cursor p = walk.at(first_group<D>(a));
   {
-    uint64_t pj = p;
+    typename W::Cursor pj = p;
+    const uint32_t lo = walk.lds_lane_offset();
     static_for<D>([&](auto J) {
-      lds_issue<POL>(buf + pj * 16, ring + J * kWave, lane);
-      pj = wrap_add(pj, kWave, n_vec);
+      lds_issue<POL>(walk.address(pj), lo, ring + J * kWave);
+      __builtin_amdgcn_sched_barrier(0);   // in the order the loop waits for them
+      pj = next_load(pj);
     });
   }
 #pragma unroll 1
-  for (uint64_t i = 1; i < iters; ++i) {
-    p = wrap_add(p, stride, n_vec);
-    uint64_t pj = p;
+  for (uint32_t i = a.iters - 1; i; --i) {
+    p = next_group(p);
+    typename W::Cursor pj = p;
+    const uint32_t lo = walk.lds_lane_offset();
     static_for<D>([&](auto J) {
       wait_vmcnt<D - 1>();
       const u32x4 v = ring[J * kWave + lane];
-      fold(v, s, x);
       wait_lgkmcnt0();      // the slot's read has returned before refill
-      lds_issue<POL>(buf + pj * 16, ring + J * kWave, lane);
-      pj = wrap_add(pj, kWave, n_vec);
+      lds_issue<POL>(walk.address(pj), lo, ring + J * kWave);
+      fold(v, s, x);
+      pj = next_load(pj);
     });
   }
   static_for<D>([&](auto J) {
@@ -114,21 +141,22 @@ __device__ __forceinline__ void async_ring_loop(const uint8_t* buf, uint64_t n_v
 
 // Matched plain ring: the same D requests in flight, loaded into registers,
 // then written to the lane's LDS slot and read back before folding.
-template <int D, int POL>
-__device__ __forceinline__ void matched_ring_loop(const uint8_t* buf, uint64_t n_vec,
-                                                  uint64_t Q, uint64_t stride,
-                                                  uint32_t wid, uint32_t n_waves,
-                                                  uint32_t lane, u32x4* ring,
+template <int D, class W>
+__device__ __forceinline__ void matched_ring_loop(const Share& a, uint32_t lane, u32x4* ring,
                                                   uint32_t& s, uint32_t& x) {
-  const uint64_t iters = groups_of(wid, Q, n_waves);
-  if (iters == 0) return;
-  uint64_t p = ((uint64_t)wid * (D * kWave)) % n_vec;
+  if (a.iters == 0) return;
+  const W walk(a.buf, a.bytes, lane);
+  const typename W::Step next_load = walk.step(kSegBytes % a.bytes, a.bytes);
+  const typename W::Step next_group = walk.step(a.stride, a.bytes);
+  typename W::Cursor p = walk.at(first_group<D>(a));
   u32x4 v[D];
   {
-    uint64_t pj = p;
+    typename W::Cursor pj = p;
+    const uint32_t lo = walk.lane_offset();
     static_for<D>([&](auto J) {
-      v[J] = load_seg<16, POL>(buf + pj * 16, lane);
-      pj = wrap_add(pj, kWave, n_vec);
+      v[J] = walk.load(pj, lo);
+      __builtin_amdgcn_sched_barrier(0);   // in the order the loop waits for them
+      pj = next_load(pj);
     });
   }
   auto through_lds = [&](int j) {
@@ -136,16 +164,19 @@ __device__ __forceinline__ void matched_ring_loop(const uint8_t* buf, uint64_t n
     compiler_fence();       // no store-to-load forwarding through LDS
     const u32x4 r = ring[j * kWave + lane];
     fold(r, s, x);
+    asm("" : "+v"(s));      // summed now: summed at the end, D vectors would wait
     compiler_fence();       // the refill below stays after this fold
   };
 #pragma unroll 1
-  for (uint64_t i = 1; i < iters; ++i) {
-    p = wrap_add(p, stride, n_vec);
-    uint64_t pj = p;
+  for (uint32_t i = a.iters - 1; i; --i) {
+    p = next_group(p);
+    typename W::Cursor pj = p;
+    const uint32_t lo = walk.lane_offset();
     static_for<D>([&](auto J) {
       through_lds(J);
-      v[J] = load_seg<16, POL>(buf + pj * 16, lane);
-      pj = wrap_add(pj, kWave, n_vec);
+      v[J] = walk.load(pj, lo);
+      __builtin_amdgcn_sched_barrier(0);   // before the wait for the next slot
+      pj = next_load(pj);
     });
   }
   static_for<D>([&](auto J) { through_lds(J); });

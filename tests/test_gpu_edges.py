@@ -98,3 +98,47 @@ def test_plain_at_the_32_bit_edges(nbytes, policy, order):
     more, morex = _prefix_sinks(words, (issued - n_vec) * 4)
     assert r["issued_loads"] == issued
     assert (r["sum32"], r["xor32"]) == ((s + more) & 0xFFFFFFFF, x ^ morex)
+
+
+@pytest.mark.parametrize("policy", [0, 1, 2, 3])
+@pytest.mark.parametrize("kind", [isw.KIND_LDS_ASYNC, isw.KIND_LDS_MATCHED])
+@pytest.mark.parametrize("nbytes,D", [(6144, 16), (1024, 1), ((1 << 32) - 3072, 5),
+                                      ((1 << 32) + 3072, 5)])
+def test_rings_at_the_edges_of_their_walks(nbytes, D, kind, policy):
+    """The LDS rings over buffers smaller than one group and on both sides of
+    4 GiB; waves with no, one and several groups."""
+    buf = dev_bytes(nbytes)
+    isw.sweep_fill_u32(buf, nbytes, SEED + 4)
+    n_vec = nbytes // 16
+    L = n_vec + 64 * 1000 + 77
+    print("ring", kind, nbytes, "policy", policy, flush=True)
+    call = isw.sweep_lds_async if kind == isw.KIND_LDS_ASYNC else isw.sweep_lds_matched_plain
+    r = call(buf, nbytes, D, 16, 3, L, isw.make_opts(cache_policy=policy))
+    issued = 64 * D * (L // (64 * D))
+    words = buf.view(torch.int32)
+    turns, rest = divmod(issued, n_vec)
+    s, x = _prefix_sinks(words, nbytes // 4)
+    more, morex = _prefix_sinks(words, rest * 4)
+    assert r["issued_loads"] == issued
+    assert (r["sum32"], r["xor32"]) == ((turns * s + more) & 0xFFFFFFFF,
+                                        (x if turns % 2 else 0) ^ morex)
+
+
+@pytest.mark.parametrize("kind_b", [isw.KIND_PLAIN, isw.KIND_LDS_ASYNC])
+@pytest.mark.parametrize("split", [False, True])
+@pytest.mark.parametrize("nbytes", [(1 << 33) - 4096, (1 << 33) + 4096])
+def test_two_streams_around_4_gib_each(nbytes, split, kind_b):
+    buf = dev_bytes(nbytes)
+    isw.sweep_fill_u32(buf, nbytes, SEED + 5)
+    half, D = nbytes // 32, 7                     # vectors of a stream's region
+    L = 2 * (half + 64 * 500 + 5)
+    print("two streams", nbytes, "split", split, "kind_b", kind_b, flush=True)
+    call = isw.sweep_two_stream_split if split else isw.sweep_two_stream_kind
+    rs = call(buf, nbytes, D, 4, 2, kind_b, L, isw.make_opts(cache_policy=3))
+    issued = 64 * D * (L // 2 // (64 * D))
+    words = buf.view(torch.int32)
+    for r, part in zip(rs, (words[:half * 4], words[half * 4:])):
+        s, x = _prefix_sinks(part, half * 4)
+        more, morex = _prefix_sinks(part, (issued - half) * 4)
+        assert r["issued_loads"] == issued
+        assert (r["sum32"], r["xor32"]) == ((s + more) & 0xFFFFFFFF, x ^ morex)
