@@ -13,6 +13,14 @@ namespace ilp {
 constexpr int kMaxK = 16;
 constexpr int kPlainWgThreads = 256;   // 4 waves, one per SIMD
 
+// Per-cell result reduced on the device from the wave records.
+struct alignas(16) CellRes {
+  uint64_t sum;   // low 32 bits used
+  uint64_t xr;    // low 32 bits used
+  uint64_t tmin;
+  uint64_t tmax;
+};
+
 // Plain K-load cell.  Round robin (and strided): wave w of n_waves handles
 // wave-groups q = w, w + n_waves, ... below Q, iters of them and one more if
 // w < extra; blocked: q = w*G .. w*G + G - 1.  All steps are in bytes: load j
@@ -102,6 +110,17 @@ struct ReduceArgs {
   sweep_wave_rec_t* rec;
 };
 
+// Its finish: `n` partial pairs into *sum, `n_rec` wave records into *out;
+// both results are device or pinned host memory.
+struct ReduceFinishArgs {
+  const float* partials;
+  uint32_t n;
+  double* sum;
+  const sweep_wave_rec_t* rec;
+  uint64_t n_rec;
+  CellRes* out;
+};
+
 // Pointer chase: buf[idx] holds the next index (32-bit words); `out`
 // receives {final index, wall t0, wall t1, shader-clock t0, shader-clock t1}.
 constexpr uint32_t kMaxChaseSamples = 4096;
@@ -156,14 +175,6 @@ struct XcdSplitArgs {
   sweep_wave_rec_t* rec;   // device [popcount(mask) * per_xcd]
 };
 
-// Per-cell result reduced on the device from the wave records.
-struct alignas(16) CellRes {
-  uint64_t sum;   // low 32 bits used
-  uint64_t xr;    // low 32 bits used
-  uint64_t tmin;
-  uint64_t tmax;
-};
-
 // Folding of wave records into cell results: cell c owns records
 // [offsets[c], offsets[c+1]).  The offsets of one or two cells travel in the
 // argument block (`offsets` null); those of more lie where the device can
@@ -215,7 +226,6 @@ hipError_t launch_finish_cells(const FinishArgs& a, uint32_t n_cells, hipStream_
 hipError_t launch_read_clock(uint64_t* out, hipStream_t st);
 // `loads` (4 or 8) 16-byte loads in flight per lane per iteration.
 const void* reduce_kernel(int dtype, int loads);
-hipError_t launch_reduce_finish(const float* partials, uint32_t n,
-                                double* out, hipStream_t st);
+hipError_t launch_finish_reduce(const ReduceFinishArgs& a, hipStream_t st);
 
 }  // namespace ilp

@@ -383,26 +383,47 @@ const void* reduce_kernel(int dtype, int loads) {
   return nullptr;
 }
 
-// Final combine in FP64, in a fixed order: thread t sums partial pairs
-// t, t+256, ... and the 256 totals are added up a fixed binary tree.
-__global__ __launch_bounds__(256) void reduce_finish(const float* partials,
-                                                     uint32_t n, double* out) {
-  __shared__ double sd[256];
-  double acc = 0.0;
-  for (uint32_t i = threadIdx.x; i < n; i += 256)
-    acc += (double)partials[2 * i] + (double)partials[2 * i + 1];
-  sd[threadIdx.x] = acc;
-  __syncthreads();
-  for (uint32_t h = 128; h > 0; h >>= 1) {
-    if (threadIdx.x < h) sd[threadIdx.x] += sd[threadIdx.x + h];
-    __syncthreads();
+// Workgroup 0 combines the partial pairs in FP64, in a fixed order: thread t
+// of 256 sums pairs t, t+256, ... and the 256 totals are added up a fixed
+// binary tree.  Workgroup 1 folds the wave records beside it.  Both are
+// latency bound, and as two launches of one workgroup each they cost 3.6 and
+// 4.9 us and the gap between them; the pairs of a thread are read eight at a
+// time.
+constexpr int kPairBatch = 8;
+
+__global__ __launch_bounds__(kFinishThreads) void finish_reduce(ReduceFinishArgs a) {
+  if (blockIdx.x == 1) {
+    fold_records(a.rec, 0, a.n_rec, a.out);
+    return;
   }
-  if (threadIdx.x == 0) out[0] = sd[0];
+  __shared__ double sd[256];
+  const uint32_t t = threadIdx.x;
+  if (t >= 256) return;                  // whole waves; the barriers below count the rest
+  const float2* pairs = reinterpret_cast<const float2*>(a.partials);
+  double acc = 0.0;
+  for (uint32_t b = t; b < a.n; b += kPairBatch * 256) {
+    float2 p[kPairBatch];
+#pragma unroll
+    for (int u = 0; u < kPairBatch; ++u) {
+      const uint32_t i = b + u * 256;
+      p[u] = pairs[i < a.n ? i : a.n - 1];
+    }
+#pragma unroll
+    for (int u = 0; u < kPairBatch; ++u)
+      if (b + u * 256 < a.n) acc += (double)p[u].x + (double)p[u].y;
+  }
+  sd[t] = acc;
+  __syncthreads();
+  if (t < kWave) {
+    // sd[t] + sd[t + 128], then + 64, 32, .. 1: the tree's pairs in its order
+    double v = (sd[t] + sd[t + 128]) + (sd[t + 64] + sd[t + 192]);
+    for (int h = kWave / 2; h > 0; h >>= 1) v += __shfl_down(v, h);
+    if (t == 0) a.sum[0] = v;
+  }
 }
 
-hipError_t launch_reduce_finish(const float* partials, uint32_t n, double* out,
-                                hipStream_t st) {
-  hipLaunchKernelGGL(reduce_finish, dim3(1), dim3(256), 0, st, partials, n, out);
+hipError_t launch_finish_reduce(const ReduceFinishArgs& a, hipStream_t st) {
+  hipLaunchKernelGGL(finish_reduce, dim3(2), dim3(kFinishThreads), 0, st, a);
   return hipGetLastError();
 }
 

@@ -57,8 +57,7 @@ struct Dev {
   size_t res_h_cap = 0;
   float* partials = nullptr;
   size_t partials_cap = 0;
-  double* dsum = nullptr;
-  double* dsum_h = nullptr;
+  double* dsum_h = nullptr;   // the precision sum, pinned like res_h
   uint64_t* clk = nullptr;
   uint64_t* chase_out = nullptr;  // 5 words per chase call
   uint64_t* walk_out = nullptr;   // 4 words per walker
@@ -126,7 +125,6 @@ void release_device(Dev* d) {
   if (d->rec) (void)hipFree(d->rec);
   if (d->res_h) (void)hipHostFree(d->res_h);
   if (d->partials) (void)hipFree(d->partials);
-  if (d->dsum) (void)hipFree(d->dsum);
   if (d->dsum_h) (void)hipHostFree(d->dsum_h);
   if (d->clk) (void)hipFree(d->clk);
   if (d->chase_out) (void)hipFree(d->chase_out);
@@ -143,8 +141,7 @@ int setup_device(Dev* d) {
   // scratch for the largest default grid (32 waves per CU)
   SW_TRY(ensure_dev(d->rec, d->rec_cap, (size_t)d->num_cus * 32));
   SW_TRY(ensure_host(d->res_h, d->res_h_cap, 64));
-  size_t one = 0, one_h = 0, clk_cap = 0;
-  SW_TRY(ensure_dev(d->dsum, one, 1));
+  size_t one_h = 0, clk_cap = 0;
   SW_TRY(ensure_host(d->dsum_h, one_h, 1));
   SW_TRY(ensure_dev(d->clk, clk_cap, 1));
   size_t chase_cap = 0;
@@ -1228,12 +1225,10 @@ int sweep_reduce_fp(const void* payload, size_t n_elems, int dtype,
   a.partials = d->partials;
   a.rec = d->rec;
   hipStream_t st = as_stream(opt);
-  FinishArgs fin;
-  SW_TRY(finish_args(*d, d->rec, {0ull, (uint64_t)grid * 4}, &fin));
   HIP_TRY(launch_timed(fn, grid, 256u, 0, st, a, d->start, d->ev[0]));
-  HIP_TRY(launch_reduce_finish(d->partials, grid, d->dsum, st));
-  HIP_TRY(launch_finish_cells(fin, 1, st));
-  HIP_TRY(hipMemcpyAsync(d->dsum_h, d->dsum, sizeof(double), hipMemcpyDeviceToHost, st));
+  HIP_TRY(launch_finish_reduce(ReduceFinishArgs{d->partials, grid, d->dsum_h, d->rec,
+                                                (uint64_t)grid * 4, d->res_h},
+                               st));
   HIP_TRY(hipEventRecord(d->ev[1], st));
   HIP_TRY(hipEventSynchronize(d->ev[1]));
   *sum = *d->dsum_h;

@@ -142,3 +142,16 @@ def test_two_streams_around_4_gib_each(nbytes, split, kind_b):
         more, morex = _prefix_sinks(part, (issued - half) * 4)
         assert r["issued_loads"] == issued
         assert (r["sum32"], r["xor32"]) == ((s + more) & 0xFFFFFFFF, x ^ morex)
+
+
+@pytest.mark.parametrize("wgs", [1, 2, 255, 256, 257, 2047, 2048, 2049, 5000])
+def test_reduce_finish_takes_every_pair_and_record(wgs):
+    """The final combine at the edges of its 256 threads and of their batches
+    of eight pairs, on integers whose sums FP32 holds exactly."""
+    n = 64 * 4 * 4 * 4 * wgs + 999          # a full group per wave, and a rest
+    g = torch.Generator(device="cuda").manual_seed(wgs)
+    p = torch.randint(-8, 9, (n,), device="cuda", generator=g).float()
+    print("reduce", wgs, "workgroups", flush=True)
+    total, r = isw.sweep_reduce_fp(p, n, isw.F32, 8, isw.make_opts(grid_wgs=wgs))
+    assert total == float(p.double().sum())
+    assert r["waves"] == 4 * wgs and r["window_ticks"] > 0
