@@ -186,6 +186,19 @@ struct FinishArgs {
   uint64_t few[3];
 };
 
+// Its finish: the fold of the n_rec records (below 2^32) into *out, and the
+// index of the first record that was not written, or not by the XCD it
+// should be from, into *first_bad (all ones if there is none).  Records come
+// in runs of `run` per XCD, going round the n_xcds XCDs of `xcds` (four bits
+// each, the first one lowest).
+struct XcdFinishArgs {
+  const sweep_wave_rec_t* rec;
+  uint64_t n_rec;
+  CellRes* out;
+  uint64_t* first_bad;
+  uint32_t run, n_xcds, xcds;
+};
+
 // ---- static scratch of the allocation-free entry point (static_scratch.hip)
 // Layout: per-wave records, then the cell result.  512 KiB + 256 bytes per
 // device.
@@ -223,6 +236,7 @@ hipError_t launch_fill(uint32_t* buf, uint64_t n_words, uint64_t seed,
                        hipStream_t st);
 // One workgroup per cell.
 hipError_t launch_finish_cells(const FinishArgs& a, uint32_t n_cells, hipStream_t st);
+hipError_t launch_finish_xcd(const XcdFinishArgs& a, hipStream_t st);
 hipError_t launch_read_clock(uint64_t* out, hipStream_t st);
 // `loads` (4 or 8) 16-byte loads in flight per lane per iteration.
 const void* reduce_kernel(int dtype, int loads);

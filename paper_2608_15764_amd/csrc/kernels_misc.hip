@@ -122,9 +122,10 @@ __device__ __forceinline__ Window wave_window(Window w) {
 }
 
 // Folds records [i0, i1) over a workgroup of kFinishThreads threads; thread
-// 0 stores the result.
+// 0 stores the result.  look(i, v, t) sees every record, as its two halves.
+template <class Look>
 __device__ __forceinline__ void fold_records(const sweep_wave_rec_t* rec, uint64_t i0,
-                                             uint64_t i1, CellRes* out) {
+                                             uint64_t i1, CellRes* out, Look look) {
   __shared__ Window part[kFinishThreads / kWave];
   Window w = no_records();
   const u32x4* r = reinterpret_cast<const u32x4*>(rec);
@@ -147,6 +148,7 @@ __device__ __forceinline__ void fold_records(const sweep_wave_rec_t* rec, uint64
         const uint64_t t1 = ((uint64_t)t[u].w << 32) | t[u].z;
         w.lo = t0 < w.lo ? t0 : w.lo;
         w.hi = t1 > w.hi ? t1 : w.hi;
+        look(i + u * kFinishThreads, v[u], t[u]);
       }
     }
   }
@@ -166,6 +168,10 @@ __device__ __forceinline__ void fold_records(const sweep_wave_rec_t* rec, uint64
   }
 }
 
+struct LookAway {
+  __device__ __forceinline__ void operator()(uint64_t, u32x4, u32x4) const {}
+};
+
 __global__ __launch_bounds__(kFinishThreads) void finish_cells(FinishArgs a) {
   const uint32_t c = blockIdx.x;
   uint64_t i0 = c == 0 ? a.few[0] : a.few[1], i1 = c == 0 ? a.few[1] : a.few[2];
@@ -173,11 +179,40 @@ __global__ __launch_bounds__(kFinishThreads) void finish_cells(FinishArgs a) {
     i0 = a.offsets[c];
     i1 = a.offsets[c + 1];
   }
-  fold_records(a.rec, i0, i1, a.out + c);
+  fold_records(a.rec, i0, i1, a.out + c, LookAway());
 }
 
 hipError_t launch_finish_cells(const FinishArgs& a, uint32_t n_cells, hipStream_t st) {
   hipLaunchKernelGGL(finish_cells, dim3(n_cells), dim3(kFinishThreads), 0, st, a);
+  return hipGetLastError();
+}
+
+// One XCD read: the fold, and the first record that is missing (a cleared
+// one has t1 = 0) or not from the XCD its number names.  Fetching up to 256 KiB
+// of records to check them on the host took 10 to 29 us of a call: 64 MiB by
+// six XCDs at 8 waves per CU 62 -> 32 us, 1 GiB by all of them at 16 199 ->
+// 180 us.
+__global__ __launch_bounds__(kFinishThreads) void finish_xcd(XcdFinishArgs a) {
+  __shared__ uint64_t first[kFinishThreads / kWave];
+  uint64_t bad = ~0ull;
+  fold_records(a.rec, 0, a.n_rec, a.out, [&](uint64_t i, u32x4 v, u32x4 t) {
+    const uint32_t slot = ((uint32_t)i / a.run) % a.n_xcds;
+    const uint32_t want = (a.xcds >> (4 * slot)) & 0xFu;
+    if ((t.z | t.w) == 0u || (v.w & 0xFu) != want) bad = i < bad ? i : bad;
+  });
+  const auto less = [](uint64_t p, uint64_t q) { return q < p ? q : p; };
+  bad = wave_fold64(bad, less);
+  const uint32_t lane = lane_id();
+  if (lane == 0) first[threadIdx.x / kWave] = bad;
+  __syncthreads();
+  if (threadIdx.x < kWave) {
+    bad = wave_fold64(lane < kFinishThreads / kWave ? first[lane] : ~0ull, less);
+    if (lane == 0) a.first_bad[0] = bad;
+  }
+}
+
+hipError_t launch_finish_xcd(const XcdFinishArgs& a, hipStream_t st) {
+  hipLaunchKernelGGL(finish_xcd, dim3(1), dim3(kFinishThreads), 0, st, a);
   return hipGetLastError();
 }
 
@@ -393,7 +428,7 @@ constexpr int kPairBatch = 8;
 
 __global__ __launch_bounds__(kFinishThreads) void finish_reduce(ReduceFinishArgs a) {
   if (blockIdx.x == 1) {
-    fold_records(a.rec, 0, a.n_rec, a.out);
+    fold_records(a.rec, 0, a.n_rec, a.out, LookAway());
     return;
   }
   __shared__ double sd[256];

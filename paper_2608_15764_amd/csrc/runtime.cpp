@@ -499,37 +499,49 @@ void xcd_account(Prepared* p, uint64_t n_act, uint64_t groups, uint32_t it_min,
   p->plan.pub.iters_max = it_max;
 }
 
+// The XCDs of a mask, four bits each, lowest first.
+uint32_t xcd_list(uint32_t mask) {
+  uint32_t list = 0, n = 0;
+  for (uint32_t x = 0; x < 8; ++x)
+    if ((mask >> x) & 1u) list |= x << (4 * n++);
+  return list;
+}
+
 // One XCD read: records (the caller's or the library's, cleared first),
-// the launch with dispatch-stamped events, the finishing kernel, one
-// synchronisation, then a check that active wave i wrote its record from
-// XCD want[i]: if the dispatcher did not put one workgroup of each round of
-// eight on every XCD, the dense numbering does not hold, groups were read
+// the launch with dispatch-stamped events, the finishing kernel, which also
+// checks that active wave i wrote its record from the XCD its number names
+// (runs of `run` waves going round the XCDs of `mask`), and one
+// synchronisation: if the dispatcher did not put one workgroup of each round
+// of eight on every XCD, the dense numbering does not hold, groups were read
 // twice or not at all, and the call fails instead of reporting a rate.
 template <class Args>
 int xcd_run(Dev& d, const sweep_opts_t* opt, Prepared& p, uint64_t n_act, Args& a,
-            const std::vector<uint8_t>& want, sweep_result_t* out) {
+            uint32_t mask, uint32_t run, sweep_result_t* out) {
   SW_TRY(check_outputs(opt, n_act));
   sweep_wave_rec_t* wave_out = opt ? opt->wave_out : nullptr;
   if (!wave_out) SW_TRY(ensure_dev(d.rec, d.rec_cap, n_act));
   a.rec = wave_out ? wave_out : d.rec;
   SW_TRY(ensure_events(d, 2));
   hipStream_t st = as_stream(opt);
-  FinishArgs fin;
-  SW_TRY(finish_args(d, a.rec, {0ull, n_act}, &fin));
+  uint64_t* first_bad = reinterpret_cast<uint64_t*>(d.res_h + 1);
+  const XcdFinishArgs fin{a.rec, n_act, d.res_h, first_bad, run,
+                          (uint32_t)__builtin_popcount(mask), xcd_list(mask)};
   HIP_TRY(launch_clear_records(a.rec, n_act, st));
   HIP_TRY(launch_timed(p.fn, p.grid, p.threads, p.lds, st, a, d.start, d.ev[0]));
-  HIP_TRY(launch_finish_cells(fin, 1, st));
+  HIP_TRY(launch_finish_xcd(fin, st));
   HIP_TRY(hipEventRecord(d.ev[1], st));
   HIP_TRY(hipEventSynchronize(d.ev[1]));
-  std::vector<sweep_wave_rec_t> h(n_act);
-  HIP_TRY(hipMemcpy(h.data(), a.rec, n_act * sizeof(sweep_wave_rec_t), hipMemcpyDeviceToHost));
-  for (uint64_t i = 0; i < n_act; ++i)
-    if (h[i].t0 == 0 || (h[i].xcc_id & 0xFu) != want[i])
-      return fail(SWEEP_ENODEV, "active wave " + std::to_string(i) +
-                                    (h[i].t0 == 0 ? " wrote no record"
-                                                  : " ran on XCD " + std::to_string(h[i].xcc_id & 0xFu) +
-                                                        ", not " + std::to_string(want[i])) +
-                                    ": workgroups were not dealt one per XCD per round of eight");
+  if (*first_bad < n_act) {
+    const uint64_t i = *first_bad;
+    sweep_wave_rec_t r;
+    HIP_TRY(hipMemcpy(&r, a.rec + i, sizeof(r), hipMemcpyDeviceToHost));
+    const uint32_t want = (fin.xcds >> (4 * ((uint32_t)i / run % fin.n_xcds))) & 0xFu;
+    return fail(SWEEP_ENODEV, "active wave " + std::to_string(i) +
+                                  (r.t1 == 0 ? " wrote no record"
+                                             : " ran on XCD " + std::to_string(r.xcc_id & 0xFu) +
+                                                   ", not " + std::to_string(want)) +
+                                  ": workgroups were not dealt one per XCD per round of eight");
+  }
   float ms = 0;
   HIP_TRY(hipEventElapsedTime(&ms, d.start, d.ev[0]));
   fill_result(d, p, d.res_h[0], ms, out);
@@ -1308,11 +1320,7 @@ int sweep_xcd_subset(const void* buf, size_t bytes, int waves_per_cu, uint32_t x
   XcdArgs a{static_cast<const uint8_t*>(buf), groups, n_act, xcd_mask, pop, nullptr};
   // active wave w belongs to workgroup w / 4, the (w / 4) mod pop-th active
   // XCD of its round
-  std::vector<uint8_t> bits, want(n_act);
-  for (uint8_t x = 0; x < 8; ++x)
-    if ((xcd_mask >> x) & 1u) bits.push_back(x);
-  for (uint64_t w = 0; w < n_act; ++w) want[w] = bits[(w / 4) % pop];
-  return xcd_run(*d, opt, p, n_act, a, want, out);
+  return xcd_run(*d, opt, p, n_act, a, xcd_mask, kPlainWgThreads / 64, out);
 }
 
 int sweep_xcd_split(const void* buf, size_t bytes, int waves_per_cu, const double* weights,
@@ -1353,11 +1361,7 @@ int sweep_xcd_split(const void* buf, size_t bytes, int waves_per_cu, const doubl
   if (a.mask == 0) return fail(SWEEP_EINVAL, "every share rounds to zero groups");
   const uint64_t n_act = (uint64_t)__builtin_popcount(a.mask) * per_xcd;
   xcd_account(&p, n_act, acc, it_min, it_max);
-  std::vector<uint8_t> bits, want(n_act);
-  for (uint8_t x = 0; x < 8; ++x)
-    if ((a.mask >> x) & 1u) bits.push_back(x);
-  for (uint64_t w = 0; w < n_act; ++w) want[w] = bits[w / per_xcd];
-  return xcd_run(*d, opt, p, n_act, a, want, out);
+  return xcd_run(*d, opt, p, n_act, a, a.mask, per_xcd, out);
 }
 
 int sweep_chase_walkers(const void* chain, size_t bytes, const uint32_t* starts,
