@@ -398,7 +398,8 @@ int sweep_batched(const sweep_cell_t* cells, int n, const sweep_opts_t* opt,
 
 /* A sweep captured once into a hipGraph and replayed (as sweep_batched, no
  * passage of the paper defines it): one kernel node per cell, in order,
- * then one finishing kernel.  The graph owns its scratch
+ * then one finishing kernel.  (Up to four launches replay faster as launches
+ * on the stream, and do so, with the same results.)  The graph owns its scratch
  * (wave records, per-cell results, offsets; 32 B per wave plus 40 B per
  * cell), so other library calls between replays do not disturb it.  The
  * cells' buffers must stay allocated until the graph is destroyed; their

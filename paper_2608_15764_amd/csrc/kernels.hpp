@@ -176,14 +176,15 @@ struct XcdSplitArgs {
 };
 
 // Folding of wave records into cell results: cell c owns records
-// [offsets[c], offsets[c+1]).  The offsets of one or two cells travel in the
-// argument block (`offsets` null); those of more lie where the device can
+// [offsets[c], offsets[c+1]).  The offsets of up to kFewCells cells travel in
+// the argument block (`offsets` null); those of more lie where the device can
 // read them.  `out` is device or pinned host memory.
+constexpr size_t kFewCells = 64;
 struct FinishArgs {
   const sweep_wave_rec_t* rec;
   const uint64_t* offsets;
   CellRes* out;
-  uint64_t few[3];
+  uint32_t few[kFewCells + 1];
 };
 
 // Its finish: the fold of the n_rec records (below 2^32) into *out, and the

@@ -174,10 +174,13 @@ struct LookAway {
 
 __global__ __launch_bounds__(kFinishThreads) void finish_cells(FinishArgs a) {
   const uint32_t c = blockIdx.x;
-  uint64_t i0 = c == 0 ? a.few[0] : a.few[1], i1 = c == 0 ? a.few[1] : a.few[2];
+  uint64_t i0, i1;
   if (a.offsets) {
     i0 = a.offsets[c];
     i1 = a.offsets[c + 1];
+  } else {
+    i0 = a.few[c];
+    i1 = a.few[c + 1];
   }
   fold_records(a.rec, i0, i1, a.out + c, LookAway());
 }

@@ -57,6 +57,8 @@ struct Dev {
   size_t res_h_cap = 0;
   float* partials = nullptr;
   size_t partials_cap = 0;
+  CellRes* spare = nullptr;   // a destroyed graph's pinned results, for the next one
+  size_t spare_cap = 0;
   double* dsum_h = nullptr;   // the precision sum, pinned like res_h
   uint64_t* clk = nullptr;
   uint64_t* chase_out = nullptr;  // 5 words per chase call
@@ -78,6 +80,8 @@ struct Dev {
 
 std::mutex g_mu;
 std::map<int, Dev*> g_devs;
+
+constexpr size_t kSpareCells = 4096;   // results a spare pinned block may hold (128 KiB)
 
 template <class T>
 int ensure_dev(T*& p, size_t& cap, size_t n) {
@@ -125,6 +129,7 @@ void release_device(Dev* d) {
   if (d->rec) (void)hipFree(d->rec);
   if (d->res_h) (void)hipHostFree(d->res_h);
   if (d->partials) (void)hipFree(d->partials);
+  if (d->spare) (void)hipHostFree(d->spare);
   if (d->dsum_h) (void)hipHostFree(d->dsum_h);
   if (d->clk) (void)hipFree(d->clk);
   if (d->chase_out) (void)hipFree(d->chase_out);
@@ -335,21 +340,26 @@ std::vector<uint64_t> record_offsets(const std::vector<Prepared>& ps) {
   return o;
 }
 
-// The finishing launch's arguments for the cells whose records are split at
-// `offs` (n + 1 entries): up to two cells carry the offsets themselves, more
-// read them from the device's pinned copy.  Neither needs a copy in front of
-// the cells, whose two dispatch gaps cost a small cell about 20 us.
+// The finishing launch's arguments for cells whose records are split at
+// `offs` (n + 1 entries): up to kFewCells cells carry the offsets in the
+// launch (true), more have them put where the device can read them (false).
+bool few_offsets(const std::vector<uint64_t>& offs, FinishArgs* a) {
+  if (offs.size() > kFewCells + 1 || offs.back() > UINT32_MAX) return false;
+  a->offsets = nullptr;
+  for (size_t i = 0; i < offs.size(); ++i) a->few[i] = (uint32_t)offs[i];
+  return true;
+}
+
+// Neither way needs a copy in front of the cells, whose two dispatch gaps cost
+// a small cell about 20 us.
 int finish_args(Dev& d, const sweep_wave_rec_t* rec, const std::vector<uint64_t>& offs,
                 FinishArgs* out) {
-  FinishArgs a{rec, nullptr, d.res_h, {0, 0, 0}};
-  if (offs.size() <= 3) {
-    std::copy(offs.begin(), offs.end(), a.few);
-  } else {
-    SW_TRY(ensure_host(d.offs_h, d.offs_h_cap, offs.size()));
-    std::copy(offs.begin(), offs.end(), d.offs_h);
-    a.offsets = d.offs_h;
-  }
-  *out = a;
+  out->rec = rec;
+  out->out = d.res_h;
+  if (few_offsets(offs, out)) return SWEEP_OK;
+  SW_TRY(ensure_host(d.offs_h, d.offs_h_cap, offs.size()));
+  std::copy(offs.begin(), offs.end(), d.offs_h);
+  out->offsets = d.offs_h;
   return SWEEP_OK;
 }
 
@@ -894,7 +904,13 @@ int sweep_plain_noalloc(const void* buf, size_t bytes, int K, int vec_width,
   // by the sweep kernel, the result by the finish
   CellRes r;
   HIP_TRY(enqueue(p, st, rec, opt ? opt->lane_out : nullptr, nullptr, nullptr));
-  HIP_TRY(launch_finish_cells(FinishArgs{rec, nullptr, res, {0, waves, 0}}, 1, st));
+  FinishArgs fin;
+  fin.rec = rec;
+  fin.offsets = nullptr;
+  fin.out = res;
+  fin.few[0] = 0;
+  fin.few[1] = (uint32_t)waves;
+  HIP_TRY(launch_finish_cells(fin, 1, st));
   HIP_TRY(hipMemcpyAsync(&r, res, sizeof(r), hipMemcpyDeviceToHost, st));
   HIP_TRY(hipStreamSynchronize(st));
   fill_result(*d, p, r, 0.0, out);
@@ -902,34 +918,6 @@ int sweep_plain_noalloc(const void* buf, size_t bytes, int K, int vec_width,
 }
 
 }  // extern "C"
-
-// A captured sweep with its own scratch (see sweep_graph_create).
-struct sweep_graph {
-  int ordinal = -1;
-  std::vector<Prepared> ps;
-  sweep_wave_rec_t* rec = nullptr;
-  CellRes* res_h = nullptr;     // pinned: the finishing node writes it
-  uint64_t* offs = nullptr;
-  FusedPoint* pts = nullptr;    // point lists of the fused launches
-  size_t fused_launches = 0;
-  std::vector<hipEvent_t> ev;   // start, end of a launch
-  hipGraph_t graph = nullptr;
-  hipGraphExec_t exec = nullptr;
-};
-
-namespace {
-
-void free_graph(sweep_graph* g) {
-  if (!g) return;
-  if (g->exec) (void)hipGraphExecDestroy(g->exec);
-  if (g->graph) (void)hipGraphDestroy(g->graph);
-  for (auto e : g->ev) (void)hipEventDestroy(e);
-  if (g->rec) (void)hipFree(g->rec);
-  if (g->offs) (void)hipFree(g->offs);
-  if (g->pts) (void)hipFree(g->pts);
-  if (g->res_h) (void)hipHostFree(g->res_h);
-  delete g;
-}
 
 // A run of consecutive cells launched together: one cell alone, or (with
 // opts->fuse) plain fixed-work round-robin cells that share the kernel and
@@ -939,7 +927,57 @@ struct LaunchGroup {
   const void* fused = nullptr;   // fused kernel, or null for a lone cell
   size_t pt0 = 0;                // index of its first point in the point list
   const uint8_t* base = nullptr; // lowest point buffer (points are offsets from it)
+  uint64_t total_groups = 0;     // of its points
 };
+
+// Sweeps of this many launches and fewer are replayed as launches on the
+// stream.  A hipGraphLaunch takes 28 us or more of a replay, whatever it
+// holds; a launch on the stream 2.3, so with a finishing launch each: one
+// launch 16 against 31 us, four 24 against 32, eight 34 against 34, sixteen
+// 53 against 46.
+constexpr size_t kDirectLaunches = 4;
+
+// A captured sweep with its own scratch (see sweep_graph_create).
+struct sweep_graph {
+  int ordinal = -1;
+  std::vector<Prepared> ps;
+  std::vector<uint64_t> offs_h;   // record offsets per cell
+  std::vector<LaunchGroup> groups;
+  FinishArgs fin;
+  sweep_wave_rec_t* rec = nullptr;
+  CellRes* res_h = nullptr;       // pinned: the finishing launch writes it
+  size_t res_h_cap = 0;
+  uint64_t* offs = nullptr;       // offs_h on the device, if not in `fin`
+  FusedPoint* pts = nullptr;      // point lists of the fused launches
+  std::vector<hipEvent_t> ev;     // start, end of a launch
+  hipGraph_t graph = nullptr;
+  hipGraphExec_t exec = nullptr;  // null: replayed as launches
+};
+
+namespace {
+
+// A graph's pinned results come from its device's spare block if that is free
+// and large enough, and go back to it (one block at most is kept, until the
+// library shuts down): allocating and freeing pinned memory takes 23 us.
+void free_graph(sweep_graph* g) {
+  if (!g) return;
+  if (g->exec) (void)hipGraphExecDestroy(g->exec);
+  if (g->graph) (void)hipGraphDestroy(g->graph);
+  for (auto e : g->ev) (void)hipEventDestroy(e);
+  if (g->rec) (void)hipFree(g->rec);
+  if (g->offs) (void)hipFree(g->offs);
+  if (g->pts) (void)hipFree(g->pts);
+  if (g->res_h) {
+    auto it = g_devs.find(g->ordinal);
+    if (it != g_devs.end() && it->second->spare_cap < g->res_h_cap &&
+        g->res_h_cap <= kSpareCells) {
+      std::swap(it->second->spare, g->res_h);
+      std::swap(it->second->spare_cap, g->res_h_cap);
+    }
+    if (g->res_h) (void)hipHostFree(g->res_h);
+  }
+  delete g;
+}
 
 bool fusable(const Prepared& p) {
   return p.c.kind == SWEEP_KIND_PLAIN && p.c.mode == SWEEP_FIXED_WORK &&
@@ -987,6 +1025,7 @@ int plan_groups(const std::vector<Prepared>& ps, bool fuse, std::vector<LaunchGr
           g0 += fp.Q;
           pts->push_back(fp);
         }
+        lg.total_groups = g0;
       } else {
         lg.count = 1;     // the fused kernel cannot reach the residency: alone
         j = i + 1;
@@ -996,6 +1035,23 @@ int plan_groups(const std::vector<Prepared>& ps, bool fuse, std::vector<LaunchGr
     i = j;
   }
   return SWEEP_OK;
+}
+
+// Enqueues a graph's launches and its finishing launch.
+hipError_t enqueue_graph(const sweep_graph& g, hipStream_t st) {
+  for (const LaunchGroup& lg : g.groups) {
+    const Prepared& p0 = g.ps[lg.first];
+    sweep_wave_rec_t* rec = g.rec + g.offs_h[lg.first];
+    hipError_t e;
+    if (lg.fused) {
+      const FusedArgs a{lg.base, g.pts + lg.pt0, lg.total_groups, rec};
+      e = launch_timed(lg.fused, p0.grid, p0.threads, p0.lds, st, a, nullptr, nullptr);
+    } else {
+      e = enqueue(p0, st, rec, nullptr, nullptr, nullptr);
+    }
+    if (e != hipSuccess) return e;
+  }
+  return launch_finish_cells(g.fin, (uint32_t)g.ps.size(), st);
 }
 
 int create_graph(Dev& d, const sweep_cell_t* cells, int n, const sweep_opts_t* opt,
@@ -1010,23 +1066,40 @@ int create_graph(Dev& d, const sweep_cell_t* cells, int n, const sweep_opts_t* o
     free_graph(g);
     return rc;
   }
-  const std::vector<uint64_t> offs = record_offsets(g->ps);
+  g->offs_h = record_offsets(g->ps);
   auto fail_g = [&](int code, const std::string& msg) {
     free_graph(g);
     return fail(code, msg);
   };
-  const size_t n_rec = std::max<uint64_t>(offs.back(), 1);
-  if (hipMalloc(reinterpret_cast<void**>(&g->rec), n_rec * sizeof(sweep_wave_rec_t)) != hipSuccess ||
-      hipMalloc(reinterpret_cast<void**>(&g->offs), offs.size() * sizeof(uint64_t)) != hipSuccess ||
-      hipHostMalloc(reinterpret_cast<void**>(&g->res_h), (size_t)n * sizeof(CellRes), hipHostMallocCoherent) != hipSuccess) {
+  const size_t n_rec = std::max<uint64_t>(g->offs_h.back(), 1);
+  if (d.spare_cap >= (size_t)n) {
+    std::swap(g->res_h, d.spare);
+    std::swap(g->res_h_cap, d.spare_cap);
+  } else {
+    rc = ensure_host(g->res_h, g->res_h_cap, std::max<size_t>((size_t)n, kFewCells));
+    if (rc != SWEEP_OK) {
+      free_graph(g);
+      return rc;
+    }
+  }
+  if (hipMalloc(reinterpret_cast<void**>(&g->rec), n_rec * sizeof(sweep_wave_rec_t)) != hipSuccess) {
     (void)hipGetLastError();
     return fail_g(SWEEP_ENOMEM, "graph scratch allocation failed");
   }
-  if (hipMemcpy(g->offs, offs.data(), offs.size() * sizeof(uint64_t), hipMemcpyHostToDevice) != hipSuccess)
-    return fail_g(SWEEP_EHIP, "graph offsets upload failed");
-  std::vector<LaunchGroup> groups;
+  g->fin.rec = g->rec;
+  g->fin.out = g->res_h;
+  if (!few_offsets(g->offs_h, &g->fin)) {
+    const size_t b = g->offs_h.size() * sizeof(uint64_t);
+    if (hipMalloc(reinterpret_cast<void**>(&g->offs), b) != hipSuccess) {
+      (void)hipGetLastError();
+      return fail_g(SWEEP_ENOMEM, "graph scratch allocation failed");
+    }
+    if (hipMemcpy(g->offs, g->offs_h.data(), b, hipMemcpyHostToDevice) != hipSuccess)
+      return fail_g(SWEEP_EHIP, "graph offsets upload failed");
+    g->fin.offsets = g->offs;
+  }
   std::vector<FusedPoint> pts;
-  rc = plan_groups(g->ps, opt && opt->fuse, &groups, &pts);
+  rc = plan_groups(g->ps, opt && opt->fuse, &g->groups, &pts);
   if (rc != SWEEP_OK) {
     free_graph(g);
     return rc;
@@ -1045,38 +1118,24 @@ int create_graph(Dev& d, const sweep_cell_t* cells, int n, const sweep_opts_t* o
       return fail_g(SWEEP_EHIP, "graph record clear failed");
   }
   g->ev.resize(2, nullptr);
-  for (auto& e : g->ev)
-    if (hipEventCreate(&e) != hipSuccess) return fail_g(SWEEP_EHIP, "hipEventCreate failed");
-  if (!d.capture && hipStreamCreateWithFlags(&d.capture, hipStreamNonBlocking) != hipSuccess)
-    return fail_g(SWEEP_EHIP, "capture stream creation failed");
-  if (hipStreamBeginCapture(d.capture, hipStreamCaptureModeThreadLocal) != hipSuccess)
-    return fail_g(SWEEP_EHIP, "hipStreamBeginCapture failed");
-  hipError_t cap_err = hipSuccess;
-  for (size_t k = 0; k < groups.size() && cap_err == hipSuccess; ++k) {
-    const LaunchGroup& lg = groups[k];
-    const Prepared& p0 = g->ps[lg.first];
-    if (!lg.fused) {
-      cap_err = enqueue(p0, d.capture, g->rec + offs[lg.first], nullptr, nullptr, nullptr);
-      continue;
-    }
-    FusedArgs a;
-    a.base = lg.base;
-    a.pts = g->pts + lg.pt0;
-    a.total_groups = pts[lg.pt0 + lg.count - 1].g0 + pts[lg.pt0 + lg.count - 1].Q;
-    a.rec = g->rec + offs[lg.first];
-    cap_err = launch_timed(lg.fused, p0.grid, p0.threads, p0.lds, d.capture, a, nullptr, nullptr);
-    ++g->fused_launches;
+  // the start event marks a time only
+  if (hipEventCreateWithFlags(&g->ev[0], hipEventDisableSystemFence) != hipSuccess ||
+      hipEventCreate(&g->ev[1]) != hipSuccess)
+    return fail_g(SWEEP_EHIP, "hipEventCreate failed");
+  if (g->groups.size() > kDirectLaunches) {
+    if (!d.capture && hipStreamCreateWithFlags(&d.capture, hipStreamNonBlocking) != hipSuccess)
+      return fail_g(SWEEP_EHIP, "capture stream creation failed");
+    if (hipStreamBeginCapture(d.capture, hipStreamCaptureModeThreadLocal) != hipSuccess)
+      return fail_g(SWEEP_EHIP, "hipStreamBeginCapture failed");
+    const hipError_t cap_err = enqueue_graph(*g, d.capture);
+    const hipError_t end_err = hipStreamEndCapture(d.capture, &g->graph);
+    if (cap_err != hipSuccess || end_err != hipSuccess)
+      return fail_g(SWEEP_EHIP, std::string("graph capture failed: ") +
+                                    hipGetErrorString(cap_err != hipSuccess ? cap_err : end_err));
+    const hipError_t ie = hipGraphInstantiate(&g->exec, g->graph, nullptr, nullptr, 0);
+    if (ie != hipSuccess)
+      return fail_g(SWEEP_EHIP, std::string("hipGraphInstantiate: ") + hipGetErrorString(ie));
   }
-  if (cap_err == hipSuccess)
-    cap_err = launch_finish_cells(FinishArgs{g->rec, g->offs, g->res_h, {0, 0, 0}}, (uint32_t)n,
-                                  d.capture);
-  hipError_t end_err = hipStreamEndCapture(d.capture, &g->graph);
-  if (cap_err != hipSuccess || end_err != hipSuccess)
-    return fail_g(SWEEP_EHIP, std::string("graph capture failed: ") +
-                                  hipGetErrorString(cap_err != hipSuccess ? cap_err : end_err));
-  hipError_t ie = hipGraphInstantiate(&g->exec, g->graph, nullptr, nullptr, 0);
-  if (ie != hipSuccess)
-    return fail_g(SWEEP_EHIP, std::string("hipGraphInstantiate: ") + hipGetErrorString(ie));
   *out = g;
   return SWEEP_OK;
 }
@@ -1086,7 +1145,11 @@ int launch_graph(Dev& d, sweep_graph* g, hipStream_t st, sweep_result_t* results
   const size_t n = g->ps.size();
   hipEvent_t e_start = g->ev[0], e_end = g->ev[1];
   HIP_TRY(hipEventRecord(e_start, st));
-  HIP_TRY(hipGraphLaunch(g->exec, st));
+  if (g->exec) {
+    HIP_TRY(hipGraphLaunch(g->exec, st));
+  } else {
+    HIP_TRY(enqueue_graph(*g, st));
+  }
   HIP_TRY(hipEventRecord(e_end, st));
   HIP_TRY(hipEventSynchronize(e_end));
   float ms = 0;
@@ -1115,7 +1178,13 @@ int sweep_graph_launch(sweep_graph_t* graph, void* stream, sweep_result_t* resul
   std::lock_guard<std::mutex> lk(g_mu);
   Dev* d = nullptr;
   SW_TRY(init_device(graph->ordinal, &d));
-  return launch_graph(*d, graph, static_cast<hipStream_t>(stream), results, graph_ms);
+  // a graph knows its device, a launch takes the current one
+  int cur = graph->ordinal;
+  if (!graph->exec) HIP_TRY(hipGetDevice(&cur));
+  if (cur != graph->ordinal) HIP_TRY(hipSetDevice(graph->ordinal));
+  const int rc = launch_graph(*d, graph, static_cast<hipStream_t>(stream), results, graph_ms);
+  if (cur != graph->ordinal) (void)hipSetDevice(cur);
+  return rc;
 }
 
 int sweep_graph_destroy(sweep_graph_t* graph) {

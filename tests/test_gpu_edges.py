@@ -48,22 +48,50 @@ def test_finish_folds_every_record(wgs):
     assert r["window_ticks"] == int(h["t1"].max() - h["t0"].min())
 
 
-@pytest.mark.parametrize("n", [1, 2, 3, 7])
+@pytest.mark.parametrize("n", [1, 4, 5, 64, 65])
 def test_cells_of_one_call_keep_apart(n):
-    """One or two cells carry their record offsets in the launch, more read
-    them from memory: the results are those of single calls either way."""
+    """Up to 64 cells carry their record offsets in the finishing launch, more
+    read them from memory; up to four launches of a graph are replayed as
+    launches.  The results are those of single calls every way, on every
+    replay."""
     nbytes = 2 << 20
     buf = dev_bytes(nbytes)
     isw.sweep_fill_u32(buf, nbytes, SEED + 2)
-    cells = [isw.make_cell(buf, nbytes, 1 + i, 16, 4 * (1 + i % 3), nbytes // 16 + 4096 * i)
+    cells = [isw.make_cell(buf, nbytes, 1 + i % 9, 16, 4 * (1 + i % 3), nbytes // 16 + 4096 * i)
              for i in range(n)]
-    many = isw.sweep_run(cells)
-    graph, _ = isw.sweep_batched(cells)
-    for c, a, b in zip(cells, many, graph):
-        one = isw.sweep_plain(buf, nbytes, c.K, 16, c.waves_per_cu, c.total_logical_loads)
-        assert (a["sum32"], a["xor32"]) == (b["sum32"], b["xor32"]) == (one["sum32"],
-                                                                       one["xor32"])
-        assert a["window_ticks"] > 0 and b["window_ticks"] > 0
+    ones = [isw.sweep_plain(buf, nbytes, c.K, 16, c.waves_per_cu, c.total_logical_loads)
+            for c in cells]
+    want = [(r["sum32"], r["xor32"]) for r in ones]
+    print("cells", n, flush=True)
+    got = [isw.sweep_run(cells), isw.sweep_batched(cells)[0]]
+    stream = torch.cuda.Stream()
+    with isw.sweep_graph_create(cells) as g:
+        for s in (None, stream, None):
+            got.append(isw.sweep_graph_launch(g, stream=s)[0])
+            torch.zeros(1000, device="cuda").add_(1)
+            torch.cuda.synchronize()
+    for rs in got:
+        assert [(r["sum32"], r["xor32"]) for r in rs] == want
+        assert all(r["window_ticks"] > 0 for r in rs)
+
+
+@pytest.mark.parametrize("runs", [1, 4, 5])
+def test_fused_runs_replay_after_each_other(runs):
+    """Fused launches, few enough to be replayed as launches and one too
+    many, of two points each."""
+    nbytes = 1 << 20
+    buf = dev_bytes(4 * nbytes)
+    isw.sweep_fill_u32(buf, 4 * nbytes, SEED + 6)
+    cells = [isw.make_cell(buf.data_ptr() + nbytes * (i % 4), nbytes, 2 + i // 2, 16, 8,
+                           nbytes // 16 + 640 * i) for i in range(2 * runs)]
+    want = [(r["sum32"], r["xor32"]) for r in isw.sweep_run(cells)]
+    print("fused runs", runs, flush=True)
+    with isw.sweep_graph_create(cells, isw.make_opts(fuse=True)) as g:
+        for _ in range(3):
+            rs, ms = isw.sweep_graph_launch(g)
+            assert [(r["sum32"], r["xor32"]) for r in rs] == want and ms > 0
+            torch.zeros(1000, device="cuda").add_(1)
+            torch.cuda.synchronize()
 
 
 def _prefix_sinks(words, n):
