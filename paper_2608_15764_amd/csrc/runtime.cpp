@@ -911,8 +911,9 @@ int sweep_plain_noalloc(const void* buf, size_t bytes, int K, int vec_width,
   fin.few[0] = 0;
   fin.few[1] = (uint32_t)waves;
   HIP_TRY(launch_finish_cells(fin, 1, st));
-  HIP_TRY(hipMemcpyAsync(&r, res, sizeof(r), hipMemcpyDeviceToHost, st));
-  HIP_TRY(hipStreamSynchronize(st));
+  // one synchronous copy on the stream: 8 us less than an asynchronous one to
+  // pageable memory and a synchronisation
+  HIP_TRY(hipMemcpyWithStream(&r, res, sizeof(r), hipMemcpyDeviceToHost, st));
   fill_result(*d, p, r, 0.0, out);
   return SWEEP_OK;
 }
@@ -1355,8 +1356,7 @@ int sweep_chase(const void* chain, size_t bytes, uint32_t start,
   hipStream_t st = static_cast<hipStream_t>(stream);
   uint64_t h[5] = {0, 0, 0, 0, 0};
   hipError_t e = launch_chase(cache_policy, st, a);
-  if (e == hipSuccess) e = hipMemcpyAsync(h, dout, sizeof(h), hipMemcpyDeviceToHost, st);
-  if (e == hipSuccess) e = hipStreamSynchronize(st);
+  if (e == hipSuccess) e = hipMemcpyWithStream(h, dout, sizeof(h), hipMemcpyDeviceToHost, st);
   if (e != hipSuccess) return fail(SWEEP_EHIP, std::string("chase: ") + hipGetErrorString(e));
   sweep_chase_t o;
   std::memset(&o, 0, sizeof(o));
@@ -1461,9 +1461,8 @@ int sweep_chase_walkers(const void* chain, size_t bytes, const uint32_t* starts,
   uint64_t h[4 * kMaxWalkers];
   hipError_t e = launch_walkers(cache_policy, st, a);
   if (e == hipSuccess)
-    e = hipMemcpyAsync(h, d->walk_out, 4 * sizeof(uint64_t) * (size_t)n_walkers,
-                       hipMemcpyDeviceToHost, st);
-  if (e == hipSuccess) e = hipStreamSynchronize(st);
+    e = hipMemcpyWithStream(h, d->walk_out, 4 * sizeof(uint64_t) * (size_t)n_walkers,
+                            hipMemcpyDeviceToHost, st);
   if (e != hipSuccess) return fail(SWEEP_EHIP, std::string("walkers: ") + hipGetErrorString(e));
   for (int i = 0; i < n_walkers; ++i) {
     const uint64_t* w = h + 4 * i;
