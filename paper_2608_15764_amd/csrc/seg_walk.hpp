@@ -16,9 +16,12 @@
 //        buffer's size, so that the wrap is a test of its sign: nine.
 //
 // The K sweep of 4-byte loads over 4 MiB (32 cells, 1 GiB read in each, 16
-// waves per CU): 4322 -> 3591 us, 8.0 -> 9.6 TB/s; 16-byte loads over 1 GiB,
-// bound by HBM, gain 1 % at 8 waves per CU.
+// waves per CU): 4322 -> 3591 us, 8.0 -> 9.6 TB/s (3442 with the loads placed
+// ahead, as the plain loop does); 16-byte loads over 1 GiB, bound by HBM, gain
+// 1 % at 8 waves per CU.
 #pragma once
+
+#include <type_traits>
 
 #include "device.hpp"
 
@@ -28,15 +31,20 @@ namespace ilp {
 // (not flat) address.
 typedef __attribute__((address_space(1))) const uint8_t* GlobalBytes;
 
-// Lane `lane`'s V bytes at base + lane * V, `base` scalar and opaque: folded
-// into one 64-bit vector address, it would cost a vector add and two
-// registers per load.
+// A segment's address, made here and kept scalar: folded into one 64-bit
+// vector address it would cost a vector add and two registers per load, and
+// carried as a cursor it would be added up in front of the load.
+__device__ __forceinline__ uint64_t scalar_address(uint64_t a) {
+  asm("" : "+s"(a));
+  return a;
+}
+
+// A lane's V bytes at seg + lane_off.
 template <int V, int POL>
-__device__ __forceinline__ typename Vec<V>::T load_global(uint64_t base, uint32_t lane_off) {
+__device__ __forceinline__ typename Vec<V>::T load_global(uint64_t seg, uint32_t lane_off) {
   typedef typename Vec<V>::T T;
   typedef __attribute__((address_space(1))) const T* P;
-  asm("" : "+s"(base));
-  const P p = (P)((GlobalBytes)base + lane_off);
+  const P p = (P)((GlobalBytes)seg + lane_off);
   if constexpr (POL == SWEEP_CACHE_NT) return __builtin_nontemporal_load(p);
   else return *p;
 }
@@ -82,9 +90,15 @@ struct NearWalk {
     if constexpr (!kBuffer) asm volatile("" : "+v"(o));
     return o;
   }
-  __device__ __forceinline__ typename Vec<V>::T load(Cursor c, uint32_t lo) const {
-    if constexpr (kBuffer) return load_buffer<V, POL>(r, lo, c);
-    else return load_global<V, POL>(base + c, lo);
+  // Where a segment's load starts: its offset in the buffer, or its address.
+  typedef std::conditional_t<kBuffer, uint32_t, uint64_t> Start;
+  __device__ __forceinline__ Start start(Cursor c) const {
+    if constexpr (kBuffer) return c;
+    else return scalar_address(base + c);
+  }
+  __device__ __forceinline__ typename Vec<V>::T load(Start at, uint32_t lo) const {
+    if constexpr (kBuffer) return load_buffer<V, POL>(r, lo, at);
+    else return load_global<V, POL>(at, lo);
   }
   // for LDS-direct requests, which are global loads under every policy
   __device__ __forceinline__ uint64_t address(Cursor c) const { return base + c; }
@@ -125,8 +139,11 @@ struct FarWalk {
     if constexpr (!kBuffer) asm volatile("" : "+v"(o));
     return o;
   }
-  __device__ __forceinline__ typename Vec<V>::T load(Cursor c, uint32_t lo) const {
-    const uint64_t seg = end + (uint64_t)c;
+  typedef uint64_t Start;
+  __device__ __forceinline__ Start start(Cursor c) const {
+    return scalar_address(end + (uint64_t)c);
+  }
+  __device__ __forceinline__ typename Vec<V>::T load(Start seg, uint32_t lo) const {
     if constexpr (kBuffer) {
       // a buffer of this one segment
       return load_buffer<V, POL>(

@@ -11,7 +11,7 @@
 // D - 1 in flight.  2 GiB, one wave per CU, depth 8 and 16: LDS-direct 590 ->
 // 555 and 505 -> 392 us, matched 780 -> 545 and 560 -> 437 under the default
 // policy (585 -> 537 and 462 -> 431 with sc1 nt); two streams of 4 waves on
-// different CUs at depth 4, 415 -> 349 us.  From 4 waves per CU and depth 8
+// different CUs at depth 4, 415 -> 336 us.  From 4 waves per CU and depth 8
 // on HBM bounds them, as before.
 #pragma once
 
@@ -80,21 +80,28 @@ __device__ __forceinline__ void plain_loop16(const Share& a, uint32_t lane, uint
   const typename W::Step next_load = walk.step(kSegBytes % a.bytes, a.bytes);
   const typename W::Step next_group = walk.step(a.stride, a.bytes);
   typename W::Cursor p = walk.at(first_group<K>(a));
+  typename W::Start at[K];      // of the next group, found while one is in flight
+  auto place = [&] {
+    typename W::Cursor pj = p;
+#pragma unroll
+    for (int j = 0; j < K; ++j) {
+      at[j] = walk.start(pj);
+      pj = next_load(pj);
+    }
+  };
+  place();
 #pragma unroll 1
   for (uint32_t i = a.iters; i; --i) {
     u32x4 v[K];
-    typename W::Cursor pj = p;
     const uint32_t lo = walk.lane_offset();
 #pragma unroll
-    for (int j = 0; j < K; ++j) {
-      v[j] = walk.load(pj, lo);
-      __builtin_amdgcn_sched_barrier(0);
-      pj = next_load(pj);
-    }
+    for (int j = 0; j < K; ++j) v[j] = walk.load(at[j], lo);
+    __builtin_amdgcn_sched_barrier(0);
+    p = next_group(p);
+    place();
     __builtin_amdgcn_sched_barrier(0);   // all K issued before any fold
 #pragma unroll
     for (int j = 0; j < K; ++j) fold(v[j], s, x);
-    p = next_group(p);
   }
 }
 
@@ -154,7 +161,7 @@ __device__ __forceinline__ void matched_ring_loop(const Share& a, uint32_t lane,
     typename W::Cursor pj = p;
     const uint32_t lo = walk.lane_offset();
     static_for<D>([&](auto J) {
-      v[J] = walk.load(pj, lo);
+      v[J] = walk.load(walk.start(pj), lo);
       __builtin_amdgcn_sched_barrier(0);   // in the order the loop waits for them
       pj = next_load(pj);
     });
@@ -174,7 +181,7 @@ __device__ __forceinline__ void matched_ring_loop(const Share& a, uint32_t lane,
     const uint32_t lo = walk.lane_offset();
     static_for<D>([&](auto J) {
       through_lds(J);
-      v[J] = walk.load(pj, lo);
+      v[J] = walk.load(walk.start(pj), lo);
       __builtin_amdgcn_sched_barrier(0);   // before the wait for the next slot
       pj = next_load(pj);
     });
