@@ -51,14 +51,14 @@ constexpr uint64_t kFarBytes = 1ull << 32;
 // launch shape: one persistent launch over their concatenated wave-groups.
 // Point p owns global groups [g0, g0 + Q); wave w of n_waves handles global
 // groups w, w + n_waves, ... (round robin over the concatenation), reading
-// load j of its point's local group q at vector (q*K + j)*64 mod n_vec.
-// `stride` = (n_waves*K*64) mod n_vec is a wave's vector step between two
-// of its groups inside one point.  Wave w's record for point p is
+// load j of its point's local group q at segment (q*K + j) mod the point's
+// size.  Steps and sizes are in bytes; `stride` = n_waves*K segments, mod
+// `bytes`, lies between two of a wave's groups inside one point.  Wave w's record for point p is
 // rec[p*n_waves + w]; records of points a wave never reaches are left as
 // they are (cleared once, before the first launch, to "empty").
 struct FusedPoint {
   uint64_t off;            // the point's buffer: FusedArgs::base + off
-  uint64_t n_vec;
+  uint64_t bytes;
   uint64_t Q;
   uint64_t g0;
   uint64_t stride;
@@ -215,8 +215,9 @@ hipError_t static_scratch(int ordinal, uint8_t** ptr);
 // unknown combination.
 // plain (kernels_plain.hip); `far` for buffers of kFarBytes and more
 const void* plain_kernel(int K, int V, int policy, bool far);
-// fused plain batch (kernels_fused.hip)
-const void* fused_kernel(int K, int V, int policy);
+// fused plain batch (kernels_fused.hip), in the form for n_waves waves;
+// `far` if a point has kFarBytes or more
+const void* fused_kernel(int K, int V, int policy, uint64_t n_waves, bool far);
 const void* xcd_kernel(int policy);
 const void* xcd_split_kernel(int policy);
 // Set `n` records to "empty" (zero sinks, t0 = all ones, t1 = 0), which

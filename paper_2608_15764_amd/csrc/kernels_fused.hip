@@ -11,6 +11,7 @@
 
 #include "device.hpp"
 #include "kernels.hpp"
+#include "seg_walk.hpp"
 
 namespace ilp {
 
@@ -26,7 +27,7 @@ __device__ __forceinline__ uint64_t uniform64(uint64_t v) {
 // argument, so loads through it stay global loads).
 struct PointRegs {
   const uint8_t* buf;
-  uint64_t n_vec, g0, end, stride;
+  uint64_t bytes, g0, end, stride;
 };
 
 // The point list is never written while the kernel runs: read it through
@@ -39,13 +40,22 @@ __device__ __forceinline__ PointRegs point_regs(const uint8_t* base, const Fused
   const auto& f = reinterpret_cast<ConstPoints>(reinterpret_cast<uintptr_t>(pts))[i];
   PointRegs r;
   r.buf = base + uniform64(f.off);
-  r.n_vec = uniform64(f.n_vec);
+  r.bytes = uniform64(f.bytes);
   r.g0 = uniform64(f.g0);
   r.end = r.g0 + uniform64(f.Q);
   r.stride = uniform64(f.stride);
   return r;
 }
 
+// Two forms of the loop.  This one steps and wraps a 64-bit offset between two
+// loads, which spaces the loads of a group by some 60 clocks; the other one
+// below issues them back to back.  Where the batch offers more bytes than HBM
+// keeps in flight anyway, spaced loads read 1-2 % faster: 64 points of 1 MiB
+// to 2 GiB, 17.5 GiB, K = 8 at 4 waves per CU (8 MiB offered) 2598 against
+// 2645 us with nt loads, 2620 against 2642 with sc1 nt; K = 4 at 16 (16 MiB)
+// 880 against 895 us for 5.5 GiB.  Below that back to back is faster: K = 3 of
+// 8 bytes at 8 waves (3 MiB), 24 points of 4 to 16 MiB, 69 against 64 us; K =
+// 3 of 16 bytes at 8 waves (6 MiB) 2680 against 2640 us for the 17.5 GiB.
 template <int K, int V, int POL>
 __global__ __launch_bounds__(kPlainWgThreads) void fused_kload(FusedArgs a) {
   const uint32_t lane = lane_id();
@@ -55,7 +65,7 @@ __global__ __launch_bounds__(kPlainWgThreads) void fused_kload(FusedArgs a) {
   // the wave's current point, cached in scalars (wave-uniform)
   uint32_t pi = 0;
   PointRegs pt = point_regs(a.base, a.pts, 0);
-  uint64_t p = 0;               // start vector of the wave's next group
+  uint64_t p = 0;               // start of the wave's next group, in bytes
   bool open = false;            // the wave has read a group of point pi
   uint32_t s = 0, x = 0;
   uint64_t t0 = 0;
@@ -74,23 +84,76 @@ __global__ __launch_bounds__(kPlainWgThreads) void fused_kload(FusedArgs a) {
       s = 0;
       x = 0;
       t0 = wall_ticks();
-      p = ((g - pt.g0) * (uint64_t)(K * kWave)) % pt.n_vec;
+      p = ((g - pt.g0) * (uint64_t)(K * kWave * V)) % pt.bytes;
     }
     typename Vec<V>::T v[K];
     uint64_t pj = p;
 #pragma unroll
     for (int j = 0; j < K; ++j) {
-      v[j] = load_seg<V, POL>(pt.buf + pj * V, lane);
-      pj += kWave;
-      if (pj >= pt.n_vec) pj -= pt.n_vec;
+      v[j] = load_seg<V, POL>(pt.buf + pj, lane);
+      pj += kWave * V;
+      if (pj >= pt.bytes) pj -= pt.bytes;
     }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int j = 0; j < K; ++j) fold(v[j], s, x);
     p += pt.stride;
-    if (p >= pt.n_vec) p -= pt.n_vec;
+    if (p >= pt.bytes) p -= pt.bytes;
   }
   if (open) wave_epilogue(s, x, t0, wall_ticks(), pi * n_waves + wid, a.rec, nullptr);
+}
+
+template <int K, int V, int POL>
+__global__ __launch_bounds__(kPlainWgThreads) void fused_kload_ahead(FusedArgs a) {
+  typedef NearWalk<V, POL> W;       // its points are below kFarBytes each
+  const uint32_t lane = lane_id();
+  const uint32_t wid = blockIdx.x * (kPlainWgThreads / kWave) + wave_in_wg();
+  const uint32_t n_waves = gridDim.x * (kPlainWgThreads / kWave);
+  const ConstPoints pts = reinterpret_cast<ConstPoints>(reinterpret_cast<uintptr_t>(a.pts));
+
+  uint64_t g = wid;                 // the wave's next group
+  for (uint32_t pi = 0; g < a.total_groups; ++pi) {
+    // the point, in scalars, addressed from the launch's base pointer (a
+    // kernel argument, so loads through it stay global loads)
+    const auto& f = pts[pi];
+    const uint64_t bytes = uniform64(f.bytes), g0 = uniform64(f.g0);
+    const uint64_t end = g0 + uniform64(f.Q);
+    if (g >= end) continue;
+    const uint64_t t0 = wall_ticks();
+    const W walk(a.base + uniform64(f.off), bytes, lane);
+    constexpr uint64_t seg = kWave * V;
+    const typename W::Step next_load = walk.step(bytes > seg ? seg : 0, bytes);
+    const typename W::Step next_group = walk.step(uniform64(f.stride), bytes);
+    uint64_t off = (g - g0) * (K * seg);
+    if (off >= bytes) off %= bytes;
+    typename W::Cursor p = walk.at(off);
+    typename W::Start at[K];        // of the next group, found while one is in flight
+    auto place = [&] {
+      typename W::Cursor pj = p;
+#pragma unroll
+      for (int j = 0; j < K; ++j) {
+        at[j] = walk.start(pj);
+        pj = next_load(pj);
+      }
+    };
+    place();
+    uint32_t s = 0, x = 0;
+#pragma unroll 1
+    do {
+      typename Vec<V>::T v[K];
+      const uint32_t lo = walk.lane_offset();
+#pragma unroll
+      for (int j = 0; j < K; ++j) v[j] = walk.load(at[j], lo);
+      __builtin_amdgcn_sched_barrier(0);
+      p = next_group(p);
+      place();
+      g += n_waves;
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int j = 0; j < K; ++j) fold(v[j], s, x);
+    } while (g < end);
+    wave_epilogue(s, x, t0, wall_ticks(), pi * n_waves + wid, a.rec, nullptr);
+  }
 }
 
 __global__ __launch_bounds__(256) void clear_records(sweep_wave_rec_t* rec, uint64_t n) {
@@ -112,19 +175,22 @@ hipError_t launch_clear_records(sweep_wave_rec_t* rec, uint64_t n, hipStream_t s
 
 namespace {
 
+// Bytes in flight up to which a group's loads go out back to back.
+constexpr uint64_t kAheadBytes = 6ull << 20;
+
 typedef void (*FusedFn)(FusedArgs);
 
 template <int V, int POL, int... Ks>
-constexpr std::array<FusedFn, sizeof...(Ks)> row(std::integer_sequence<int, Ks...>) {
-  return {&fused_kload<Ks + 1, V, POL>...};
+constexpr std::array<FusedFn, 2 * sizeof...(Ks)> row(std::integer_sequence<int, Ks...>) {
+  return {&fused_kload<Ks + 1, V, POL>..., &fused_kload_ahead<Ks + 1, V, POL>...};
 }
 
 template <int V, int POL>
 constexpr auto kRow = row<V, POL>(std::make_integer_sequence<int, kMaxK>{});
 
-// [vector width index][policy][K-1]
+// [vector width index][policy][ahead * kMaxK + K-1]
 const FusedFn* table(int vi, int pol) {
-  static const std::array<FusedFn, kMaxK> t[3][kNumPolicies] = {
+  static const std::array<FusedFn, 2 * kMaxK> t[3][kNumPolicies] = {
       {kRow<4, 0>, kRow<4, 1>, kRow<4, 2>, kRow<4, 3>},
       {kRow<8, 0>, kRow<8, 1>, kRow<8, 2>, kRow<8, 3>},
       {kRow<16, 0>, kRow<16, 1>, kRow<16, 2>, kRow<16, 3>},
@@ -136,10 +202,11 @@ int width_index(int V) { return V == 4 ? 0 : V == 8 ? 1 : V == 16 ? 2 : -1; }
 
 }  // namespace
 
-const void* fused_kernel(int K, int V, int policy) {
+const void* fused_kernel(int K, int V, int policy, uint64_t n_waves, bool far) {
   const int vi = width_index(V);
   if (vi < 0 || K < 1 || K > kMaxK || policy < 0 || policy >= kNumPolicies) return nullptr;
-  return reinterpret_cast<const void*>(table(vi, policy)[K - 1]);
+  const bool ahead = !far && n_waves * (uint64_t)(K * kWave * V) <= kAheadBytes;
+  return reinterpret_cast<const void*>(table(vi, policy)[(ahead ? kMaxK : 0) + K - 1]);
 }
 
 }  // namespace ilp

@@ -1002,7 +1002,10 @@ int plan_groups(const std::vector<Prepared>& ps, bool fuse, std::vector<LaunchGr
     lg.count = j - i;
     if (lg.count > 1) {
       const Prepared& p0 = ps[i];
-      const void* fn = fused_kernel(p0.c.K, p0.c.vec_width, p0.c.cache_policy);
+      const bool far = std::any_of(ps.begin() + i, ps.begin() + j,
+                                   [](const Prepared& p) { return p.c.bytes >= kFarBytes; });
+      const void* fn = fused_kernel(p0.c.K, p0.c.vec_width, p0.c.cache_policy,
+                                    p0.plan.pub.waves, far);
       int nb = 0;
       if (fn) HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fn, (int)p0.threads,
                                                                    p0.lds));
@@ -1019,10 +1022,10 @@ int plan_groups(const std::vector<Prepared>& ps, bool fuse, std::vector<LaunchGr
           const Prepared& p = ps[k];
           FusedPoint fp;
           fp.off = reinterpret_cast<uintptr_t>(p.c.buf) - base;
-          fp.n_vec = p.plan.pub.n_vec;
+          fp.bytes = p.plan.pub.n_vec * (uint64_t)p.c.vec_width;
           fp.Q = p.plan.pub.Q;
           fp.g0 = g0;
-          fp.stride = (nw * (uint64_t)p.c.K * 64ull) % fp.n_vec;
+          fp.stride = (nw * (uint64_t)p.c.K * 64ull) % p.plan.pub.n_vec * (uint64_t)p.c.vec_width;
           g0 += fp.Q;
           pts->push_back(fp);
         }

@@ -183,3 +183,27 @@ def test_reduce_finish_takes_every_pair_and_record(wgs):
     total, r = isw.sweep_reduce_fp(p, n, isw.F32, 8, isw.make_opts(grid_wgs=wgs))
     assert total == float(p.double().sum())
     assert r["waves"] == 4 * wgs and r["window_ticks"] > 0
+
+
+@pytest.mark.parametrize("policy", [0, 1, 2, 3])
+@pytest.mark.parametrize("V,K,w", [(4, 1, 4), (8, 5, 4), (16, 6, 4), (16, 7, 4), (16, 3, 8),
+                                   (16, 4, 8), (4, 14, 8)])
+def test_fused_forms_match_single_cells(V, K, w, policy):
+    """Both forms of the fused loop, on the sides of the 6 MiB in flight where
+    the choice changes: points of one segment, of less than a group per
+    wave, of a ragged last group and read more than once."""
+    seg = 64 * V
+    sizes = [seg, 3 * seg, 700 * seg, 4099 * seg, 20000 * seg]
+    buf = dev_bytes(sum(sizes))
+    isw.sweep_fill_u32(buf, sum(sizes), SEED + 7)
+    cells, at = [], 0
+    for i, n in enumerate(sizes):
+        loads = (1 + 2 * (i % 3)) * (n // V) + 64 * K + 77 * i
+        cells.append(isw.make_cell(buf.data_ptr() + at, n, K, V, w, loads, cache_policy=policy))
+        at += n
+    print("fused form", V, K, w, "policy", policy, flush=True)
+    want = [(r["issued_loads"], r["sum32"], r["xor32"]) for r in isw.sweep_run(cells)]
+    with isw.sweep_graph_create(cells, isw.make_opts(fuse=True)) as g:
+        for _ in range(2):
+            rs, _ = isw.sweep_graph_launch(g)
+            assert [(r["issued_loads"], r["sum32"], r["xor32"]) for r in rs] == want

@@ -277,3 +277,22 @@ def test_plain_walks_step_in_scalar_registers(plain, kernel, K, V, P):
     waits = [i for i, l in enumerate(body) if l.startswith("s_waitcnt") and "vmcnt" in l]
     assert len(loads) == K and waits[0] > loads[-1], name
     assert not any(l.startswith(("v_cmp", "v_lshl_add_u64", "flat_")) for l in body), name
+
+
+@pytest.mark.parametrize("P", [0, 1, 2, 3])
+@pytest.mark.parametrize("V", [4, 16])
+@pytest.mark.parametrize("K", [1, 6, 12])
+def test_fused_back_to_back_form_keeps_the_K_load_loop(fused, K, V, P):
+    """The fused kernel's other form: K loads of a group with nothing between
+    them, one wait after the last, no spills."""
+    text, funcs = fused
+    name = f"_ZN3ilp17fused_kload_aheadILi{K}ELi{V}ELi{P}EEEvNS_9FusedArgsE"
+    lines = funcs[name]
+    loads = [i for i, l in enumerate(lines) if LOAD.match(l)]
+    assert len(loads) == K
+    assert loads[-1] - loads[0] == K - 1 or not any(
+        l.startswith(("s_add", "s_cmp", "v_", "s_waitcnt")) for l in lines[loads[0]:loads[-1]]
+        if not LOAD.match(l))
+    assert not any(l.startswith(("scratch_", "flat_")) for l in lines), name
+    m = _meta(text, name)
+    assert m["vgpr_spill_count"] == 0 and m["private_segment_fixed_size"] == 0
