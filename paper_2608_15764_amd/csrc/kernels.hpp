@@ -240,8 +240,10 @@ hipError_t launch_fill(uint32_t* buf, uint64_t n_words, uint64_t seed,
 hipError_t launch_finish_cells(const FinishArgs& a, uint32_t n_cells, hipStream_t st);
 hipError_t launch_finish_xcd(const XcdFinishArgs& a, hipStream_t st);
 hipError_t launch_read_clock(uint64_t* out, hipStream_t st);
-// `loads` (4 or 8) 16-byte loads in flight per lane per iteration.
-const void* reduce_kernel(int dtype, int loads);
+// 16-byte loads in flight per lane: 8 at one wave per SIMD, 4 above, so that
+// at least 8 MiB is in flight at every occupancy of the default grid.
+constexpr int reduce_loads(int waves_per_cu) { return waves_per_cu == 4 ? 8 : 4; }
+const void* reduce_kernel(int dtype, int waves_per_cu);
 hipError_t launch_finish_reduce(const ReduceFinishArgs& a, hipStream_t st);
 
 }  // namespace ilp

@@ -320,11 +320,31 @@ __device__ __forceinline__ float decode_one(const uint8_t* p) {
   }
 }
 
-// NL = loads in flight per lane per iteration (4 or 8); a wave-group is
-// NL x 64 lanes x 16 bytes.
-template <int DT, int NL>
-__global__ __launch_bounds__(256) void reduce_fp(ReduceArgs a) {
+// Accumulates vectors J .. of a group in order: four of FP8, one of the others.
+// 64 e4m3 values are k * 2^-9 with |k| <= 64 * 229376 < 2^24, so their FP32
+// sum is exact; one TwoSum per 64 values (four vectors).
+template <int DT> constexpr int acc_step() { return DT == SWEEP_FP8_E4M3 ? 4 : 1; }
+template <int DT>
+__device__ __forceinline__ void acc_some(Pair& p, const u32x4* v) {
+  if constexpr (DT == SWEEP_FP8_E4M3) {
+    float t = 0.0f;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) t += fp8_vec_sum(v[j]);
+    add_term(p, t);
+  } else {
+    acc_vec<DT>(p, v[0]);
+  }
+}
+
+// NL = loads in flight per lane (4 or 8); a wave-group is NL x 64 lanes x 16
+// bytes.  RING: a vector's place is loaded again as soon as it has been
+// added, so that NL loads stay in flight through the arithmetic; otherwise the
+// group is added up before the next one is asked for.  The additions and
+// their order are the same.
+template <int DT, int NL, bool RING>
+__device__ __forceinline__ void reduce_body(const ReduceArgs& a) {
   static_assert(NL % 4 == 0, "FP8 groups of four vectors are summed exactly");
+  constexpr int S = acc_step<DT>();
   const uint64_t t0 = wall_ticks();
   const uint32_t lane = lane_id();
   const uint32_t wv = wave_in_wg();
@@ -332,28 +352,41 @@ __global__ __launch_bounds__(256) void reduce_fp(ReduceArgs a) {
   const uint32_t n_waves = gridDim.x * 4;
   Pair p{0.0f, 0.0f};
 
-  // full wave-groups; all NL loads are issued before any is consumed
-#pragma unroll 1
-  for (uint64_t g = wid; g < a.n_groups; g += n_waves) {
-    const uint8_t* base = a.payload + g * (NL * kWave * 16);
-    u32x4 v[NL];
+  const auto load = [&](uint64_t g, int j) {
+    return load_seg<16, SWEEP_CACHE_NT>(a.payload + g * (NL * kWave * 16) + j * (kWave * 16),
+                                        lane);
+  };
+  u32x4 v[NL];
+  if constexpr (RING) {
+    if (wid < a.n_groups) {
 #pragma unroll
-    for (int j = 0; j < NL; ++j)
-      v[j] = load_seg<16, SWEEP_CACHE_NT>(base + j * (kWave * 16), lane);
-    __builtin_amdgcn_sched_barrier(0);
-    if constexpr (DT == SWEEP_FP8_E4M3) {
-      // 64 e4m3 values are k * 2^-9 with |k| <= 64 * 229376 < 2^24, so
-      // their FP32 sum is exact; one TwoSum per 64 values (four vectors)
-#pragma unroll
-      for (int q = 0; q < NL / 4; ++q) {
-        float t = 0.0f;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) t += fp8_vec_sum(v[4 * q + j]);
-        add_term(p, t);
+      for (int j = 0; j < NL; ++j) {
+        v[j] = load(wid, j);
+        __builtin_amdgcn_sched_barrier(0);   // in the order they are waited for
       }
-    } else {
+#pragma unroll 1
+      for (uint64_t g = (uint64_t)wid + n_waves; g < a.n_groups; g += n_waves) {
 #pragma unroll
-      for (int j = 0; j < NL; ++j) acc_vec<DT>(p, v[j]);
+        for (int j = 0; j < NL; j += S) {
+          acc_some<DT>(p, v + j);
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int k = j; k < j + S; ++k) v[k] = load(g, k);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < NL; j += S) acc_some<DT>(p, v + j);
+    }
+  } else {
+    // full wave-groups; all NL loads are issued before any is consumed
+#pragma unroll 1
+    for (uint64_t g = wid; g < a.n_groups; g += n_waves) {
+#pragma unroll
+      for (int j = 0; j < NL; ++j) v[j] = load(g, j);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int j = 0; j < NL; j += S) acc_some<DT>(p, v + j);
     }
   }
   // remaining whole vectors, one per thread of the grid
@@ -405,6 +438,23 @@ __global__ __launch_bounds__(256) void reduce_fp(ReduceArgs a) {
   }
 }
 
+template <int DT, int NL>
+__global__ __launch_bounds__(256) void reduce_fp(ReduceArgs a) {
+  reduce_body<DT, NL, false>(a);
+}
+// The ring is for BF16 at one or two waves per SIMD.  There the arithmetic of
+// a group (64 TwoSums per load of a lane) takes as long as its loads, and no
+// other wave covers either: 4 GiB at 4 waves per CU 5.75 -> 7.25 TB/s, at 8
+// 7.25 either way; 1 GiB 5.3 -> 7.0 and 6.9 -> 7.1; 64 MiB 4.3 -> 5.3 and 5.2 ->
+// 5.6.  FP32 and FP8 have fewer operations per byte and read 2 % faster in
+// batches at 4 waves (7.39 against 7.17 TB/s over 4 GiB); from 12 waves per CU
+// on the two forms are within 2 % of each other or the ring loses (BF16 over
+// 4 GiB at 32 waves 6.84 against 6.30).
+template <int NL>
+__global__ __launch_bounds__(256) void reduce_bf16_ring(ReduceArgs a) {
+  reduce_body<SWEEP_BF16, NL, true>(a);
+}
+
 template <int NL>
 const void* reduce_of(int dtype) {
   switch (dtype) {
@@ -415,10 +465,11 @@ const void* reduce_of(int dtype) {
   }
 }
 
-const void* reduce_kernel(int dtype, int loads) {
-  if (loads == 4) return reduce_of<4>(dtype);
-  if (loads == 8) return reduce_of<8>(dtype);
-  return nullptr;
+const void* reduce_kernel(int dtype, int waves_per_cu) {
+  const bool ring = dtype == SWEEP_BF16 && waves_per_cu <= 8;
+  if (reduce_loads(waves_per_cu) == 8)
+    return ring ? reinterpret_cast<const void*>(&reduce_bf16_ring<8>) : reduce_of<8>(dtype);
+  return ring ? reinterpret_cast<const void*>(&reduce_bf16_ring<4>) : reduce_of<4>(dtype);
 }
 
 // Workgroup 0 combines the partial pairs in FP64, in a fixed order: thread t

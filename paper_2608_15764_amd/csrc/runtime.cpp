@@ -1292,13 +1292,11 @@ int sweep_reduce_fp(const void* payload, size_t n_elems, int dtype,
   a.payload = static_cast<const uint8_t*>(payload);
   a.n_bytes = (uint64_t)n_elems * esz;
   a.n_vec = a.n_bytes / 16;
-  // Loads in flight per lane: 8 at one wave per SIMD, 4 above, so that at
-  // least 8 MiB is in flight at every occupancy of the default grid.
-  const int loads = waves_per_cu == 4 ? 8 : 4;
+  const int loads = reduce_loads(waves_per_cu);
   a.n_groups = a.n_vec / (64u * (uint64_t)loads);
   if (a.n_vec - a.n_groups * 64u * (uint64_t)loads > (uint64_t)grid * 256)
     return fail(SWEEP_EINVAL, "grid too small for the ragged remainder");
-  const void* fn = reduce_kernel(dtype, loads);
+  const void* fn = reduce_kernel(dtype, waves_per_cu);
   if (!fn) return fail(SWEEP_EINVAL, "no reduction kernel for this dtype");
   hipFuncAttributes fa;
   HIP_TRY(hipFuncGetAttributes(&fa, fn));

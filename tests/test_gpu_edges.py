@@ -207,3 +207,22 @@ def test_fused_forms_match_single_cells(V, K, w, policy):
         for _ in range(2):
             rs, _ = isw.sweep_graph_launch(g)
             assert [(r["issued_loads"], r["sum32"], r["xor32"]) for r in rs] == want
+
+
+@pytest.mark.parametrize("w", [4, 8, 12])
+@pytest.mark.parametrize("groups", [0, 1, 2, 3, 7])
+@pytest.mark.parametrize("rest", [0, 1, 8, 511])
+def test_bf16_sum_by_groups_per_wave(groups, rest, w):
+    """The BF16 sum where a wave has no, one, two and more groups (the ring's
+    start, its first turn and its drain), on integers: the sums are exact."""
+    loads = 8 if w == 4 else 4
+    waves = 8 * 4
+    n = (groups * waves + (groups + 1) // 2) * loads * 64 * 8 + rest
+    if n == 0:
+        n = 8
+    g = torch.Generator(device="cuda").manual_seed(n)
+    p = torch.randint(-8, 9, (n,), device="cuda", generator=g).to(torch.bfloat16)
+    print("bf16 sum", n, "waves per CU", w, flush=True)
+    total, r = isw.sweep_reduce_fp(p, n, isw.BF16, w, isw.make_opts(grid_wgs=8))
+    assert total == float(p.double().sum())
+    assert r["waves"] == waves and r["issued_bytes"] == 2 * n

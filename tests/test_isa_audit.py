@@ -296,3 +296,17 @@ def test_fused_back_to_back_form_keeps_the_K_load_loop(fused, K, V, P):
     assert not any(l.startswith(("scratch_", "flat_")) for l in lines), name
     m = _meta(text, name)
     assert m["vgpr_spill_count"] == 0 and m["private_segment_fixed_size"] == 0
+
+
+@pytest.mark.parametrize("NL", [4, 8])
+def test_reduce_ring_waits_for_one_vector_at_a_time(misc, NL):
+    """The ring form of the BF16 sum reloads a vector's registers as soon as
+    it is added: every wait of the loop leaves NL - 1 loads in flight."""
+    text, funcs = misc
+    name = f"_ZN3ilp16reduce_bf16_ringILi{NL}EEEvNS_10ReduceArgsE"
+    body = _loop(funcs[name])
+    assert sum(bool(LOAD.match(l)) for l in body) == NL
+    waits = [l for l in body if l.startswith("s_waitcnt") and "vmcnt" in l]
+    assert len(waits) == NL and all(f"vmcnt({NL - 1})" in l for l in waits), waits
+    m = _meta(text, name)
+    assert m["vgpr_spill_count"] == 0 and m["private_segment_fixed_size"] == 0
