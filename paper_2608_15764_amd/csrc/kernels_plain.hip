@@ -16,7 +16,7 @@
 
 namespace ilp {
 
-template <int K, int V, int POL, template <int, int> class Walk>
+template <int K, int V, int POL, template <int, int> class Walk, bool SPACED>
 __device__ __forceinline__ void plain_cell(const PlainArgs& a) {
   const uint64_t t0 = wall_ticks();
   const uint32_t lane = lane_id();
@@ -42,11 +42,6 @@ __device__ __forceinline__ void plain_cell(const PlainArgs& a) {
     // the first group's start; most lie inside the buffer
     uint64_t off = q0 * a.gstep;
     if (off >= a.bytes) off %= a.bytes;
-    // Where the K loads of a group start is worked out while the group
-    // before it is in flight, so that they are issued back to back: found
-    // between them, K = 2 / 4 / 8 / 14 loads of 4 bytes over 1 GiB at 4 waves
-    // per CU (sc1 nt) took 891 / 520 / 322 / 228 us, and take 864 / 463 /
-    // 275 / 192.  Cells that HBM bounds do not change.
     typename W::Cursor p = walk.at(off);
     typename W::Start at[K];
     auto place = [&] {
@@ -57,18 +52,31 @@ __device__ __forceinline__ void plain_cell(const PlainArgs& a) {
         pj = next_load(pj);
       }
     };
+    // The K loads go into K register sets, all of them before the first is
+    // folded (the barrier: without it the scheduler may refill registers
+    // early to raise occupancy).  Where the next group's loads start is worked
+    // out while this one's are in flight, so that a group goes out at once:
+    // 1 GiB in 4-byte loads at 4 waves per CU, K = 2 / 4 / 8 / 14, 891 / 520 /
+    // 322 / 228 us with the steps between the loads, 864 / 463 / 275 / 192 with
+    // them ahead; 16-byte loads, 4 waves, K = 4, 5460 -> 6150 GB/s.
     place();
 #pragma unroll 1
     for (; iters; --iters) {
       typename Vec<V>::T v[K];
       const uint32_t lo = walk.lane_offset();
 #pragma unroll
-      for (int j = 0; j < K; ++j) v[j] = walk.load(at[j], lo);
+      for (int j = 0; j < K; ++j) {
+        v[j] = walk.load(at[j], lo);
+        if (SPACED && j + 1 < K) {
+          // 16 idle cycles; see the rule at plain_kernel
+          __builtin_amdgcn_sched_barrier(0);
+          asm volatile("s_nop 15");
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
       __builtin_amdgcn_sched_barrier(0);
       p = next_group(p);
       place();
-      // all K loads are issued before the first is consumed: without this
-      // barrier the scheduler may refill registers early to raise occupancy
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int j = 0; j < K; ++j) {
@@ -85,13 +93,25 @@ __device__ __forceinline__ void plain_cell(const PlainArgs& a) {
 
 template <int K, int V, int POL>
 __global__ __launch_bounds__(kPlainWgThreads) void plain_kload(PlainArgs a) {
-  plain_cell<K, V, POL, NearWalk>(a);
+  plain_cell<K, V, POL, NearWalk, false>(a);
 }
 
-// The same cell over 4 GiB and more.
+// The same cell with a gap between the loads of a group, for cells that
+// saturate HBM.
+template <int K, int V, int POL>
+__global__ __launch_bounds__(kPlainWgThreads) void plain_kload_spaced(PlainArgs a) {
+  plain_cell<K, V, POL, NearWalk, true>(a);
+}
+
+// The same cells over 4 GiB and more.
 template <int K, int V, int POL>
 __global__ __launch_bounds__(kPlainWgThreads) void plain_kload_far(PlainArgs a) {
-  plain_cell<K, V, POL, FarWalk>(a);
+  plain_cell<K, V, POL, FarWalk, false>(a);
+}
+
+template <int K, int V, int POL>
+__global__ __launch_bounds__(kPlainWgThreads) void plain_kload_far_spaced(PlainArgs a) {
+  plain_cell<K, V, POL, FarWalk, true>(a);
 }
 
 namespace {
@@ -99,16 +119,17 @@ namespace {
 typedef void (*PlainFn)(PlainArgs);
 
 template <int V, int POL, int... Ks>
-constexpr std::array<PlainFn, 2 * sizeof...(Ks)> row(std::integer_sequence<int, Ks...>) {
-  return {&plain_kload<Ks + 1, V, POL>..., &plain_kload_far<Ks + 1, V, POL>...};
+constexpr std::array<PlainFn, 4 * sizeof...(Ks)> row(std::integer_sequence<int, Ks...>) {
+  return {&plain_kload<Ks + 1, V, POL>..., &plain_kload_spaced<Ks + 1, V, POL>...,
+          &plain_kload_far<Ks + 1, V, POL>..., &plain_kload_far_spaced<Ks + 1, V, POL>...};
 }
 
 template <int V, int POL>
 constexpr auto kRow = row<V, POL>(std::make_integer_sequence<int, kMaxK>{});
 
-// [vector width index][policy][far * kMaxK + K-1]
+// [vector width index][policy][(2 * far + spaced) * kMaxK + K-1]
 const PlainFn* table(int vi, int pol) {
-  static const std::array<PlainFn, 2 * kMaxK> t[3][kNumPolicies] = {
+  static const std::array<PlainFn, 4 * kMaxK> t[3][kNumPolicies] = {
       {kRow<4, 0>, kRow<4, 1>, kRow<4, 2>, kRow<4, 3>},
       {kRow<8, 0>, kRow<8, 1>, kRow<8, 2>, kRow<8, 3>},
       {kRow<16, 0>, kRow<16, 1>, kRow<16, 2>, kRow<16, 3>},
@@ -116,14 +137,35 @@ const PlainFn* table(int vi, int pol) {
   return t[vi][pol].data();
 }
 
+constexpr uint64_t kSpacedInFlight = 8ull << 20;
+constexpr uint64_t kSpacedGroup = 16ull << 10;
+constexpr uint64_t kSpacedBytes = 128ull << 20;
+
 int width_index(int V) { return V == 4 ? 0 : V == 8 ? 1 : V == 16 ? 2 : -1; }
 
 }  // namespace
 
-const void* plain_kernel(int K, int V, int policy, bool far) {
+// Which form a cell takes: more than kSpacedInFlight offered by 8 or more
+// waves per CU, or by groups of kSpacedGroup, over a buffer that the 256 MiB
+// last-level cache does not hold, goes with a gap between loads.  HBM is
+// saturated there, and K loads sent at once by so many waves reach it as
+// bursts that some strides fold onto few channels.  GB/s, back to back ->
+// spaced, 1 GiB, sc1 nt: 16 bytes, 16 waves per CU, K = 8 6390 -> 6950, K = 16
+// 5960 -> 6840; 32 waves, K = 8 6680 -> 6980; 4 waves, K = 16 (16 KiB) 6660 ->
+// 6880; 8 bytes, 16 waves, K = 6 6600 -> 7240; 28 waves, K = 3 6160 -> 6930;
+// most others within 1 %.  Below the lines the gap costs what it delays: 4
+// waves, K = 4 6150 -> 5590, K = 12 6890 -> 6680; 8 bytes, 4 waves, K = 16
+// (8 MiB in flight) 7260 -> 6260; 64 MiB, 4 waves, K = 16 6840 -> 6260.  At 192
+// MiB the two are level.  Gaps of 4 and 8 cycles lift the same cells less.
+const void* plain_kernel(int K, int V, int policy, int waves_per_cu, uint64_t n_waves,
+                         uint64_t bytes) {
   const int vi = width_index(V);
   if (vi < 0 || K < 1 || K > kMaxK || policy < 0 || policy >= kNumPolicies) return nullptr;
-  return reinterpret_cast<const void*>(table(vi, policy)[(far ? kMaxK : 0) + K - 1]);
+  const uint64_t group = (uint64_t)K * kWave * V;
+  const bool spaced = n_waves * group > kSpacedInFlight && bytes > kSpacedBytes &&
+                      (waves_per_cu >= 8 || group >= kSpacedGroup);
+  const bool far = bytes >= kFarBytes;
+  return reinterpret_cast<const void*>(table(vi, policy)[(2 * far + spaced) * kMaxK + K - 1]);
 }
 
 }  // namespace ilp

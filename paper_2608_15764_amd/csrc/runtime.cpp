@@ -244,7 +244,8 @@ int prepare(Dev& d, const sweep_cell_t& c, int pin, Prepared* out, bool cache = 
   if (c.cache_policy < 0 || c.cache_policy > 3)
     return fail(SWEEP_EINVAL, "unknown cache policy");
   const bool far = c.bytes >= kFarBytes;
-  p.fn = c.kind == SWEEP_KIND_PLAIN ? plain_kernel(c.K, c.vec_width, c.cache_policy, far)
+  p.fn = c.kind == SWEEP_KIND_PLAIN ? plain_kernel(c.K, c.vec_width, c.cache_policy,
+                                               c.waves_per_cu, p.plan.pub.waves, c.bytes)
                                     : lds_kernel(c.kind, c.K, c.cache_policy, far);
   if (!p.fn) return fail(SWEEP_EINVAL, "no kernel for this cell");
   p.grid = p.plan.pub.grid_wgs;
@@ -985,8 +986,11 @@ bool fusable(const Prepared& p) {
          p.c.order == SWEEP_ORDER_ROUND_ROBIN;
 }
 
+// (of any size: a plain kernel's form, and so its function, depends on it)
 bool same_launch(const Prepared& a, const Prepared& b) {
-  return a.fn == b.fn && a.grid == b.grid && a.threads == b.threads && a.lds == b.lds;
+  return a.c.K == b.c.K && a.c.vec_width == b.c.vec_width &&
+         a.c.cache_policy == b.c.cache_policy && a.grid == b.grid &&
+         a.threads == b.threads && a.lds == b.lds;
 }
 
 // Splits the prepared cells into launch groups and builds the fused point

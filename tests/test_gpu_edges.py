@@ -226,3 +226,45 @@ def test_bf16_sum_by_groups_per_wave(groups, rest, w):
     total, r = isw.sweep_reduce_fp(p, n, isw.BF16, w, isw.make_opts(grid_wgs=8))
     assert total == float(p.double().sum())
     assert r["waves"] == waves and r["issued_bytes"] == 2 * n
+
+
+def _wrapped_sinks(words, n_vec, issued):
+    """Sinks of `issued` 16-byte loads that walk `n_vec` vectors round."""
+    turns, rest = divmod(issued, n_vec)
+    s, x = _prefix_sinks(words, n_vec * 4)
+    more, morex = _prefix_sinks(words, rest * 4)
+    return (turns * s + more) & 0xFFFFFFFF, (x if turns & 1 else 0) ^ morex
+
+
+@pytest.mark.parametrize("order", [0, 1, 2])
+@pytest.mark.parametrize("nbytes", [(128 << 20), (128 << 20) + 1024, (1 << 32) - 1024,
+                                    (1 << 32) + 1024])
+@pytest.mark.parametrize("K,w", [(5, 4), (15, 4), (16, 4), (4, 8), (5, 8), (16, 8), (2, 16),
+                                 (3, 16), (13, 32)])
+def test_plain_forms_at_the_lines_between_them(K, w, nbytes, order):
+    """The plain loop's two forms at the lines where the choice changes: 8 MiB
+    in flight, 16 KiB groups of few waves, 128 MiB; both walks; a pass and a
+    bit, so that groups wrap."""
+    buf = dev_bytes(nbytes)
+    isw.sweep_fill_u32(buf, nbytes, SEED + 8)
+    n_vec = nbytes // 16
+    L = n_vec + 64 * K * 1000 + 77
+    print("plain form", K, w, nbytes, "order", order, flush=True)
+    r = isw.sweep_plain(buf, nbytes, K, 16, w, L, isw.make_opts(cache_policy=3, order=order))
+    issued = 64 * K * (L // (64 * K))
+    assert r["issued_loads"] == issued
+    assert (r["sum32"], r["xor32"]) == _wrapped_sinks(buf.view(torch.int32), n_vec, issued)
+
+
+def test_points_of_both_plain_forms_fuse():
+    """A fused batch of points whose single cells take different plain kernels
+    (below and above 128 MiB and 4 GiB) gives what the cells give."""
+    sizes = [96 << 20, 160 << 20, (1 << 32) + 1024]
+    buf = dev_bytes(sizes[-1])
+    isw.sweep_fill_u32(buf, sizes[-1], SEED + 9)
+    cells = [isw.make_cell(buf, n, 8, 16, 16, n // 16, cache_policy=3) for n in sizes]
+    want = [(r["issued_loads"], r["sum32"], r["xor32"]) for r in isw.sweep_run(cells)]
+    print("fused points of", sizes, flush=True)
+    with isw.sweep_graph_create(cells, isw.make_opts(fuse=True)) as g:
+        rs, _ = isw.sweep_graph_launch(g)
+    assert [(r["issued_loads"], r["sum32"], r["xor32"]) for r in rs] == want

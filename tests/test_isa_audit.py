@@ -310,3 +310,27 @@ def test_reduce_ring_waits_for_one_vector_at_a_time(misc, NL):
     assert len(waits) == NL and all(f"vmcnt({NL - 1})" in l for l in waits), waits
     m = _meta(text, name)
     assert m["vgpr_spill_count"] == 0 and m["private_segment_fixed_size"] == 0
+
+
+@pytest.mark.parametrize("P", [0, 3])
+@pytest.mark.parametrize("V", [4, 16])
+@pytest.mark.parametrize("K", [2, 9, 14, 16])
+@pytest.mark.parametrize("kernel", ["plain_kload_spaced", "plain_kload_far_spaced"])
+def test_spaced_plain_form_keeps_the_K_load_loop(plain, kernel, K, V, P):
+    """The plain loop with a gap between the loads of a group: K loads, K - 1
+    gaps, one wait after the last, and the registers of the other form's
+    residency."""
+    text, funcs = plain
+    name = f"_ZN3ilp{len(kernel)}{kernel}ILi{K}ELi{V}ELi{P}EEEvNS_9PlainArgsE"
+    body = _loop(funcs[name])
+    loads = [i for i, l in enumerate(body) if LOAD.match(l)]
+    gaps = [i for i, l in enumerate(body) if re.match(r"s_nop\s+15", l)]
+    waits = [i for i, l in enumerate(body) if l.startswith("s_waitcnt") and "vmcnt" in l]
+    assert len(loads) == K and len(gaps) == K - 1 and waits[0] > loads[-1], name
+    assert all(a < g < b for a, g, b in zip(loads, gaps, loads[1:])), name
+    m = _meta(text, name)
+    assert m["vgpr_spill_count"] == 0 and m["private_segment_fixed_size"] == 0
+    other = _meta(text, name.replace(f"{len(kernel)}{kernel}",
+                                     f"{len(kernel) - 7}{kernel[:-7]}"))
+    waves = [min(8, 512 // (8 * -(-k["vgpr_count"] // 8))) for k in (m, other)]
+    assert waves[0] == waves[1], (name, m, other)
