@@ -241,10 +241,11 @@ hipError_t launch_fill(uint32_t* buf, uint64_t n_words, uint64_t seed,
 hipError_t launch_finish_cells(const FinishArgs& a, uint32_t n_cells, hipStream_t st);
 hipError_t launch_finish_xcd(const XcdFinishArgs& a, hipStream_t st);
 hipError_t launch_read_clock(uint64_t* out, hipStream_t st);
-// 16-byte loads in flight per lane: 8 at one wave per SIMD, 4 above, so that
-// at least 8 MiB is in flight at every occupancy of the default grid.
+// 16-byte loads of a lane's group: 8 at one wave per SIMD, 4 above, so that
+// at least 8 MiB can be in flight at every occupancy of the default grid.
 constexpr int reduce_loads(int waves_per_cu) { return waves_per_cu == 4 ? 8 : 4; }
-const void* reduce_kernel(int dtype, int waves_per_cu);
+// in the form for n_waves waves over `bytes`
+const void* reduce_kernel(int dtype, int waves_per_cu, uint64_t n_waves, uint64_t bytes);
 hipError_t launch_finish_reduce(const ReduceFinishArgs& a, hipStream_t st);
 
 }  // namespace ilp

@@ -320,31 +320,27 @@ __device__ __forceinline__ float decode_one(const uint8_t* p) {
   }
 }
 
-// Accumulates vectors J .. of a group in order: four of FP8, one of the others.
-// 64 e4m3 values are k * 2^-9 with |k| <= 64 * 229376 < 2^24, so their FP32
-// sum is exact; one TwoSum per 64 values (four vectors).
-template <int DT> constexpr int acc_step() { return DT == SWEEP_FP8_E4M3 ? 4 : 1; }
+// Accumulates vector j (0, 1, ... in order) of a group.  64 e4m3 values are
+// k * 2^-9 with |k| <= 64 * 229376 < 2^24, so their FP32 sum is exact; one
+// TwoSum per 64 values (four vectors, whose sum so far is t).
 template <int DT>
-__device__ __forceinline__ void acc_some(Pair& p, const u32x4* v) {
+__device__ __forceinline__ void acc_one(Pair& p, float& t, const u32x4& v, int j) {
   if constexpr (DT == SWEEP_FP8_E4M3) {
-    float t = 0.0f;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) t += fp8_vec_sum(v[j]);
-    add_term(p, t);
+    t = (j % 4 ? t : 0.0f) + fp8_vec_sum(v);
+    if (j % 4 == 3) add_term(p, t);
   } else {
-    acc_vec<DT>(p, v[0]);
+    acc_vec<DT>(p, v);
   }
 }
 
-// NL = loads in flight per lane (4 or 8); a wave-group is NL x 64 lanes x 16
-// bytes.  RING: a vector's place is loaded again as soon as it has been
-// added, so that NL loads stay in flight through the arithmetic; otherwise the
-// group is added up before the next one is asked for.  The additions and
-// their order are the same.
-template <int DT, int NL, bool RING>
+// A wave-group is NL x 64 lanes x 16 bytes.  AT of its NL loads are asked for
+// at a time and added up before the next AT; with AT = 0 a ring instead: a
+// vector's place is loaded again as soon as it has been added, so that NL loads
+// stay in flight through the arithmetic.  The additions and their order are
+// the same for every AT.
+template <int DT, int NL, int AT>
 __device__ __forceinline__ void reduce_body(const ReduceArgs& a) {
   static_assert(NL % 4 == 0, "FP8 groups of four vectors are summed exactly");
-  constexpr int S = acc_step<DT>();
   const uint64_t t0 = wall_ticks();
   const uint32_t lane = lane_id();
   const uint32_t wv = wave_in_wg();
@@ -356,9 +352,10 @@ __device__ __forceinline__ void reduce_body(const ReduceArgs& a) {
     return load_seg<16, SWEEP_CACHE_NT>(a.payload + g * (NL * kWave * 16) + j * (kWave * 16),
                                         lane);
   };
-  u32x4 v[NL];
-  if constexpr (RING) {
+  float t = 0.0f;
+  if constexpr (AT == 0) {
     if (wid < a.n_groups) {
+      u32x4 v[NL];
 #pragma unroll
       for (int j = 0; j < NL; ++j) {
         v[j] = load(wid, j);
@@ -367,26 +364,30 @@ __device__ __forceinline__ void reduce_body(const ReduceArgs& a) {
 #pragma unroll 1
       for (uint64_t g = (uint64_t)wid + n_waves; g < a.n_groups; g += n_waves) {
 #pragma unroll
-        for (int j = 0; j < NL; j += S) {
-          acc_some<DT>(p, v + j);
+        for (int j = 0; j < NL; ++j) {
+          acc_one<DT>(p, t, v[j], j);
           __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-          for (int k = j; k < j + S; ++k) v[k] = load(g, k);
+          v[j] = load(g, j);
           __builtin_amdgcn_sched_barrier(0);
         }
       }
 #pragma unroll
-      for (int j = 0; j < NL; j += S) acc_some<DT>(p, v + j);
+      for (int j = 0; j < NL; ++j) acc_one<DT>(p, t, v[j], j);
     }
   } else {
-    // full wave-groups; all NL loads are issued before any is consumed
+    // full wave-groups; AT loads are issued before any is consumed
 #pragma unroll 1
     for (uint64_t g = wid; g < a.n_groups; g += n_waves) {
 #pragma unroll
-      for (int j = 0; j < NL; ++j) v[j] = load(g, j);
-      __builtin_amdgcn_sched_barrier(0);
+      for (int j = 0; j < NL; j += AT) {
+        u32x4 v[AT];
 #pragma unroll
-      for (int j = 0; j < NL; j += S) acc_some<DT>(p, v + j);
+        for (int k = 0; k < AT; ++k) v[k] = load(g, j + k);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int k = 0; k < AT; ++k) acc_one<DT>(p, t, v[k], j + k);
+        __builtin_amdgcn_sched_barrier(0);
+      }
     }
   }
   // remaining whole vectors, one per thread of the grid
@@ -440,7 +441,7 @@ __device__ __forceinline__ void reduce_body(const ReduceArgs& a) {
 
 template <int DT, int NL>
 __global__ __launch_bounds__(256) void reduce_fp(ReduceArgs a) {
-  reduce_body<DT, NL, false>(a);
+  reduce_body<DT, NL, NL>(a);
 }
 // The ring is for BF16 at one or two waves per SIMD.  There the arithmetic of
 // a group (64 TwoSums per load of a lane) takes as long as its loads, and no
@@ -452,7 +453,13 @@ __global__ __launch_bounds__(256) void reduce_fp(ReduceArgs a) {
 // 4 GiB at 32 waves 6.84 against 6.30).
 template <int NL>
 __global__ __launch_bounds__(256) void reduce_bf16_ring(ReduceArgs a) {
-  reduce_body<SWEEP_BF16, NL, true>(a);
+  reduce_body<SWEEP_BF16, NL, 0>(a);
+}
+
+// One or two loads at a time, for many waves (reduce_kernel's rule).
+template <int DT, int AT>
+__global__ __launch_bounds__(256) void reduce_fp_few(ReduceArgs a) {
+  reduce_body<DT, 4, AT>(a);
 }
 
 template <int NL>
@@ -464,12 +471,37 @@ const void* reduce_of(int dtype) {
     default: return nullptr;
   }
 }
+template <int AT>
+const void* reduce_few_of(int dtype) {
+  switch (dtype) {
+    case SWEEP_F32: return reinterpret_cast<const void*>(&reduce_fp_few<SWEEP_F32, AT>);
+    case SWEEP_BF16: return reinterpret_cast<const void*>(&reduce_fp_few<SWEEP_BF16, AT>);
+    case SWEEP_FP8_E4M3: return reinterpret_cast<const void*>(&reduce_fp_few<SWEEP_FP8_E4M3, AT>);
+    default: return nullptr;
+  }
+}
 
-const void* reduce_kernel(int dtype, int waves_per_cu) {
+// HBM reads fastest with about 6-8 MiB in flight, and four loads of each of
+// many waves are 12-32 MiB.  Payloads beyond the 256 MiB last-level cache are
+// read one load at a time from 24 MiB on, two from 12 (BF16, whose
+// arithmetic needs more cover, from 16).  TB/s, four at a time -> fewer, 4 GiB
+// of FP32 / BF16 / FP8: 12 waves per CU 7.07 -> 7.32 / 7.07 -> 6.90, not taken /
+// 7.04 -> 7.20; 16 waves 6.99 -> 7.15 / 6.96 -> 7.17 / 6.98 -> 7.02; 20 waves
+// 6.73 -> 7.05 / 6.60 -> 7.00 / 6.70 -> 7.00; 24 waves 6.53 -> 7.23 / 6.54 ->
+// 7.10 / 6.45 -> 7.11; 32 waves 6.82 -> 7.05 / 6.83 -> 6.98 / 6.84 -> 6.98.  Over
+// 512 MiB 32 waves gain nothing (FP32 and BF16 1 % slower), so their line is
+// there; over 128 MiB most lose 1-5 %.
+const void* reduce_kernel(int dtype, int waves_per_cu, uint64_t n_waves, uint64_t bytes) {
   const bool ring = dtype == SWEEP_BF16 && waves_per_cu <= 8;
   if (reduce_loads(waves_per_cu) == 8)
     return ring ? reinterpret_cast<const void*>(&reduce_bf16_ring<8>) : reduce_of<8>(dtype);
-  return ring ? reinterpret_cast<const void*>(&reduce_bf16_ring<4>) : reduce_of<4>(dtype);
+  if (ring) return reinterpret_cast<const void*>(&reduce_bf16_ring<4>);
+  const uint64_t mib = n_waves * (4 * kWave * 16) >> 20;    // four loads of every wave
+  if (bytes > (mib >= 32 ? 512ull << 20 : 256ull << 20)) {
+    if (mib >= 24) return reduce_few_of<1>(dtype);
+    if (mib >= (dtype == SWEEP_BF16 ? 16 : 12)) return reduce_few_of<2>(dtype);
+  }
+  return reduce_of<4>(dtype);
 }
 
 // Workgroup 0 combines the partial pairs in FP64, in a fixed order: thread t

@@ -1300,7 +1300,7 @@ int sweep_reduce_fp(const void* payload, size_t n_elems, int dtype,
   a.n_groups = a.n_vec / (64u * (uint64_t)loads);
   if (a.n_vec - a.n_groups * 64u * (uint64_t)loads > (uint64_t)grid * 256)
     return fail(SWEEP_EINVAL, "grid too small for the ragged remainder");
-  const void* fn = reduce_kernel(dtype, waves_per_cu);
+  const void* fn = reduce_kernel(dtype, waves_per_cu, (uint64_t)grid * 4, a.n_bytes);
   if (!fn) return fail(SWEEP_EINVAL, "no reduction kernel for this dtype");
   hipFuncAttributes fa;
   HIP_TRY(hipFuncGetAttributes(&fa, fn));

@@ -268,3 +268,25 @@ def test_points_of_both_plain_forms_fuse():
     with isw.sweep_graph_create(cells, isw.make_opts(fuse=True)) as g:
         rs, _ = isw.sweep_graph_launch(g)
     assert [(r["issued_loads"], r["sum32"], r["xor32"]) for r in rs] == want
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "fp8"])
+@pytest.mark.parametrize("w,mib", [(12, 256), (12, 257), (16, 257), (20, 300), (24, 257),
+                                   (28, 300), (32, 512), (32, 513)])
+def test_sum_with_fewer_loads_at_a_time(w, mib, dtype):
+    """The sum over more than 256 MiB by many waves asks for one or two loads
+    at a time: on integers every form gives the exact sum, with a ragged last
+    group and trailing elements."""
+    dt, td, eb = {"f32": (isw.F32, torch.float32, 4), "bf16": (isw.BF16, torch.bfloat16, 2),
+                  "fp8": (isw.FP8_E4M3, torch.float8_e4m3fn, 1)}[dtype]
+    n = (mib << 20) // eb + 64 * 4 * 5 * 16 + 16 // eb - 1
+    g = torch.Generator(device="cuda").manual_seed(w * 1000 + mib)
+    ints = torch.randint(-8, 9, (n,), device="cuda", generator=g, dtype=torch.int8)
+    p = ints.to(td)
+    print("sum", dtype, n, "waves per CU", w, flush=True)
+    total, r = isw.sweep_reduce_fp(p, n, dt, w)
+    assert total == float(ints.sum(dtype=torch.int64))
+    assert r["issued_bytes"] == n * eb
+    # a grid of eight workgroups stays with four loads at a time
+    small, _ = isw.sweep_reduce_fp(p[:n // 16 * 16], n // 16 * 16, dt, w, isw.make_opts(grid_wgs=8))
+    assert small == float(ints[:n // 16 * 16].sum(dtype=torch.int64))

@@ -334,3 +334,18 @@ def test_spaced_plain_form_keeps_the_K_load_loop(plain, kernel, K, V, P):
                                      f"{len(kernel) - 7}{kernel[:-7]}"))
     waves = [min(8, 512 // (8 * -(-k["vgpr_count"] // 8))) for k in (m, other)]
     assert waves[0] == waves[1], (name, m, other)
+
+
+@pytest.mark.parametrize("AT", [1, 2])
+@pytest.mark.parametrize("DT", [0, 1, 2])
+def test_sum_with_fewer_loads_at_a_time(misc, DT, AT):
+    """The sum's form for many waves: four loads per turn of the loop, AT of
+    them before each wait for everything in flight."""
+    text, funcs = misc
+    name = f"_ZN3ilp13reduce_fp_fewILi{DT}ELi{AT}EEEvNS_10ReduceArgsE"
+    body = _loop(funcs[name])
+    kinds = ["load" if LOAD.match(l) else "wait" for l in body
+             if LOAD.match(l) or re.match(r"s_waitcnt\s+vmcnt\(0\)", l)]
+    assert kinds == (["load"] * AT + ["wait"]) * (4 // AT), (name, kinds)
+    m = _meta(text, name)
+    assert m["vgpr_spill_count"] == 0 and m["private_segment_fixed_size"] == 0
