@@ -137,33 +137,42 @@ const PlainFn* table(int vi, int pol) {
   return t[vi][pol].data();
 }
 
-constexpr uint64_t kSpacedInFlight = 8ull << 20;
-constexpr uint64_t kSpacedGroup = 16ull << 10;
-constexpr uint64_t kSpacedBytes = 128ull << 20;
-
 int width_index(int V) { return V == 4 ? 0 : V == 8 ? 1 : V == 16 ? 2 : -1; }
+
+// Which form a cell takes.  K loads sent at once by many waves reach a
+// saturated HBM as bursts that some strides fold onto few channels; a gap
+// between loads spreads them, and costs what it delays elsewhere.  Measured
+// over 1 GiB, sc1 nt, GB/s back to back -> spaced:
+//  16 bytes   from 8 MiB in flight on, by 8 or more waves per CU or in groups
+//             of 16 KiB, over a buffer that the 256 MiB last-level cache does
+//             not hold: 16 waves, K = 8 6390 -> 6950, K = 16 5960 -> 6840; 32
+//             waves, K = 8 6680 -> 6980; 4 waves, K = 16 6660 -> 6880; most
+//             others within 1 %.  Not 4 waves, K = 4 6150 -> 5590, K = 12
+//             6890 -> 6680; 64 MiB, 4 waves, K = 16 6840 -> 6260.  At 192 MiB
+//             the two are level.
+//  4, 8 bytes between 8 and 14 MiB in flight, 4 bytes from 16 waves per CU on,
+//             8 from 8; 8 bytes, 16 waves, K = 6 6600 -> 7240, 28 waves, K = 3
+//             6160 -> 6930; 4 bytes, 24 waves, K = 8 6120 -> 6890; over 64 to
+//             128 MiB the same (28 waves, K = 3 5900 -> 6600).  Not above: 24
+//             waves, K = 5 of 8 bytes (15 MiB) 7140 -> 6730, K = 10 of 4 over
+//             20 MiB 6950 -> 6780; not below: 4 waves, K = 16 of 8 bytes (8
+//             MiB) 7260 -> 6260; 12 waves, K = 12 of 4 bytes 6970 -> 6180.
+// Gaps of 4 and 8 cycles lift the same cells less.
+bool spaced_form(int K, int V, int waves_per_cu, uint64_t n_waves, uint64_t bytes) {
+  const uint64_t group = (uint64_t)K * kWave * V, in_flight = n_waves * group;
+  if (in_flight <= (8ull << 20)) return false;
+  if (V == 16)
+    return bytes > (128ull << 20) && (waves_per_cu >= 8 || group >= (16ull << 10));
+  return in_flight <= (14ull << 20) && bytes >= (64ull << 20) && waves_per_cu * V >= 64;
+}
 
 }  // namespace
 
-// Which form a cell takes: more than kSpacedInFlight offered by 8 or more
-// waves per CU, or by groups of kSpacedGroup, over a buffer that the 256 MiB
-// last-level cache does not hold, goes with a gap between loads.  HBM is
-// saturated there, and K loads sent at once by so many waves reach it as
-// bursts that some strides fold onto few channels.  GB/s, back to back ->
-// spaced, 1 GiB, sc1 nt: 16 bytes, 16 waves per CU, K = 8 6390 -> 6950, K = 16
-// 5960 -> 6840; 32 waves, K = 8 6680 -> 6980; 4 waves, K = 16 (16 KiB) 6660 ->
-// 6880; 8 bytes, 16 waves, K = 6 6600 -> 7240; 28 waves, K = 3 6160 -> 6930;
-// most others within 1 %.  Below the lines the gap costs what it delays: 4
-// waves, K = 4 6150 -> 5590, K = 12 6890 -> 6680; 8 bytes, 4 waves, K = 16
-// (8 MiB in flight) 7260 -> 6260; 64 MiB, 4 waves, K = 16 6840 -> 6260.  At 192
-// MiB the two are level.  Gaps of 4 and 8 cycles lift the same cells less.
 const void* plain_kernel(int K, int V, int policy, int waves_per_cu, uint64_t n_waves,
                          uint64_t bytes) {
   const int vi = width_index(V);
   if (vi < 0 || K < 1 || K > kMaxK || policy < 0 || policy >= kNumPolicies) return nullptr;
-  const uint64_t group = (uint64_t)K * kWave * V;
-  const bool spaced = n_waves * group > kSpacedInFlight && bytes > kSpacedBytes &&
-                      (waves_per_cu >= 8 || group >= kSpacedGroup);
+  const bool spaced = spaced_form(K, V, waves_per_cu, n_waves, bytes);
   const bool far = bytes >= kFarBytes;
   return reinterpret_cast<const void*>(table(vi, policy)[(2 * far + spaced) * kMaxK + K - 1]);
 }

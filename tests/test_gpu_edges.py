@@ -290,3 +290,26 @@ def test_sum_with_fewer_loads_at_a_time(w, mib, dtype):
     # a grid of eight workgroups stays with four loads at a time
     small, _ = isw.sweep_reduce_fp(p[:n // 16 * 16], n // 16 * 16, dt, w, isw.make_opts(grid_wgs=8))
     assert small == float(ints[:n // 16 * 16].sum(dtype=torch.int64))
+
+
+@pytest.mark.parametrize("nbytes", [(64 << 20) - 1024, 64 << 20])
+@pytest.mark.parametrize("V,K,w", [(4, 8, 16), (4, 9, 16), (4, 14, 16), (4, 15, 16), (4, 14, 12),
+                                   (8, 8, 8), (8, 9, 8), (8, 14, 8), (8, 15, 8), (8, 3, 28),
+                                   (8, 16, 4)])
+def test_plain_forms_of_narrow_loads(V, K, w, nbytes):
+    """The same for 4- and 8-byte loads, whose paced form lies between 8 and 14
+    MiB in flight: the same words as 16-byte loads of a like number of bytes."""
+    buf = dev_bytes(nbytes)
+    isw.sweep_fill_u32(buf, nbytes, SEED + 10)
+    n_vec = nbytes // V
+    L = n_vec + 64 * K * 1000 + 77
+    print("plain form", V, K, w, nbytes, flush=True)
+    r = isw.sweep_plain(buf, nbytes, K, V, w, L, isw.make_opts(cache_policy=3))
+    issued = 64 * K * (L // (64 * K))
+    assert r["issued_loads"] == issued
+    words = buf.view(torch.int32)
+    turns, rest = divmod(issued, n_vec)
+    s, x = _prefix_sinks(words, nbytes // 4)
+    more, morex = _prefix_sinks(words, rest * V // 4)
+    assert (r["sum32"], r["xor32"]) == ((turns * s + more) & 0xFFFFFFFF,
+                                        (x if turns & 1 else 0) ^ morex)
