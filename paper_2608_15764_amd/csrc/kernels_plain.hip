@@ -157,9 +157,20 @@ int width_index(int V) { return V == 4 ? 0 : V == 8 ? 1 : V == 16 ? 2 : -1; }
 //             waves, K = 5 of 8 bytes (15 MiB) 7140 -> 6730, K = 10 of 4 over
 //             20 MiB 6950 -> 6780; not below: 4 waves, K = 16 of 8 bytes (8
 //             MiB) 7260 -> 6260; 12 waves, K = 12 of 4 bytes 6970 -> 6180.
+//  strided, 16 bytes, past the L1: the loads of a group may all fall on one
+//             segment of a buffer read more than once, and then miss together
+//             where spaced ones hit: above 14 MiB in flight, and from 8 MiB on
+//             over 64 MiB and more; 4 MiB, 8 waves, K = 8 16600 -> 19360, K =
+//             16 17000 -> 21000; 16 MiB, 16 waves, K = 4 12120 -> 13780; 128
+//             MiB, 4 waves, K = 8 5250 -> 5650.  Below, 4 MiB, 8 waves, K = 3
+//             11020 -> 9750.
 // Gaps of 4 and 8 cycles lift the same cells less.
-bool spaced_form(int K, int V, int waves_per_cu, uint64_t n_waves, uint64_t bytes) {
+bool spaced_form(int K, int V, int policy, int order, int waves_per_cu, uint64_t n_waves,
+                 uint64_t bytes) {
   const uint64_t group = (uint64_t)K * kWave * V, in_flight = n_waves * group;
+  if (V == 16 && order == SWEEP_ORDER_STRIDED && policy >= SWEEP_CACHE_BYPASS_L1 &&
+      (in_flight > (14ull << 20) || (in_flight >= (8ull << 20) && bytes >= (64ull << 20))))
+    return true;
   if (in_flight <= (8ull << 20)) return false;
   if (V == 16)
     return bytes > (128ull << 20) && (waves_per_cu >= 8 || group >= (16ull << 10));
@@ -168,11 +179,11 @@ bool spaced_form(int K, int V, int waves_per_cu, uint64_t n_waves, uint64_t byte
 
 }  // namespace
 
-const void* plain_kernel(int K, int V, int policy, int waves_per_cu, uint64_t n_waves,
-                         uint64_t bytes) {
+const void* plain_kernel(int K, int V, int policy, int order, int waves_per_cu,
+                         uint64_t n_waves, uint64_t bytes) {
   const int vi = width_index(V);
   if (vi < 0 || K < 1 || K > kMaxK || policy < 0 || policy >= kNumPolicies) return nullptr;
-  const bool spaced = spaced_form(K, V, waves_per_cu, n_waves, bytes);
+  const bool spaced = spaced_form(K, V, policy, order, waves_per_cu, n_waves, bytes);
   const bool far = bytes >= kFarBytes;
   return reinterpret_cast<const void*>(table(vi, policy)[(2 * far + spaced) * kMaxK + K - 1]);
 }

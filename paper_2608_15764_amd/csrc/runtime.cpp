@@ -245,7 +245,7 @@ int prepare(Dev& d, const sweep_cell_t& c, int pin, Prepared* out, bool cache = 
     return fail(SWEEP_EINVAL, "unknown cache policy");
   const bool far = c.bytes >= kFarBytes;
   p.fn = c.kind == SWEEP_KIND_PLAIN ? plain_kernel(c.K, c.vec_width, c.cache_policy,
-                                               c.waves_per_cu, p.plan.pub.waves, c.bytes)
+                                               c.order, c.waves_per_cu, p.plan.pub.waves, c.bytes)
                                     : lds_kernel(c.kind, c.K, c.cache_policy, far);
   if (!p.fn) return fail(SWEEP_EINVAL, "no kernel for this cell");
   p.grid = p.plan.pub.grid_wgs;

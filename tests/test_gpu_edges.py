@@ -313,3 +313,21 @@ def test_plain_forms_of_narrow_loads(V, K, w, nbytes):
     more, morex = _prefix_sinks(words, rest * V // 4)
     assert (r["sum32"], r["xor32"]) == ((turns * s + more) & 0xFFFFFFFF,
                                         (x if turns & 1 else 0) ^ morex)
+
+
+@pytest.mark.parametrize("policy", [0, 2, 3])
+@pytest.mark.parametrize("nbytes,K,w", [(4 << 20, 14, 4), (4 << 20, 15, 4), (4 << 20, 16, 8),
+                                        (64 << 20, 8, 4), ((64 << 20) - 1024, 8, 4)])
+def test_strided_plain_forms(nbytes, K, w, policy):
+    """Strided cells on both sides of their own line, over whole turns of the
+    buffer: each turn's loads cover every segment once in some order."""
+    buf = dev_bytes(nbytes)
+    isw.sweep_fill_u32(buf, nbytes, SEED + 11)
+    words = buf.view(torch.int32)
+    segs = nbytes // 1024
+    L = 64 * K * segs                      # Q = segs: every load j of a group is turn j
+    print("strided form", nbytes, K, w, "policy", policy, flush=True)
+    r = isw.sweep_plain(buf, nbytes, K, 16, w, L, isw.make_opts(cache_policy=policy, order=2))
+    s, x = _prefix_sinks(words, nbytes // 4)
+    assert r["issued_loads"] == L
+    assert (r["sum32"], r["xor32"]) == ((K * s) & 0xFFFFFFFF, x if K & 1 else 0)
