@@ -83,6 +83,9 @@ std::map<int, Dev*> g_devs;
 
 constexpr size_t kSpareCells = 4096;   // results a spare pinned block may hold (128 KiB)
 
+// Scratch of at least n items, grown by giving up the shorter block first.  A
+// growth that fails leaves none, so a call ensures what it hands to a kernel,
+// also what setup_device has made large enough.
 template <class T>
 int ensure_dev(T*& p, size_t& cap, size_t n) {
   if (n <= cap) return SWEEP_OK;
@@ -352,9 +355,10 @@ bool few_offsets(const std::vector<uint64_t>& offs, FinishArgs* a) {
 }
 
 // Neither way needs a copy in front of the cells, whose two dispatch gaps cost
-// a small cell about 20 us.
+// a small cell about 20 us.  The results go to d.res_h, one per cell.
 int finish_args(Dev& d, const sweep_wave_rec_t* rec, const std::vector<uint64_t>& offs,
                 FinishArgs* out) {
+  SW_TRY(ensure_host(d.res_h, d.res_h_cap, offs.size() - 1));
   out->rec = rec;
   out->out = d.res_h;
   if (few_offsets(offs, out)) return SWEEP_OK;
@@ -437,7 +441,6 @@ int run_prepared(Dev& d, std::vector<Prepared>& ps, hipStream_t st,
   const size_t n = ps.size();
   const std::vector<uint64_t> offs = record_offsets(ps);
   if (!wave_out) SW_TRY(ensure_dev(d.rec, d.rec_cap, offs[n]));
-  SW_TRY(ensure_host(d.res_h, d.res_h_cap, n));
   SW_TRY(ensure_events(d, n + 1));
   sweep_wave_rec_t* rec = wave_out ? wave_out : d.rec;
   if (wave_out && n != 1) return fail(SWEEP_EINVAL, "wave_out takes a single cell");
@@ -532,6 +535,7 @@ int xcd_run(Dev& d, const sweep_opts_t* opt, Prepared& p, uint64_t n_act, Args& 
   sweep_wave_rec_t* wave_out = opt ? opt->wave_out : nullptr;
   if (!wave_out) SW_TRY(ensure_dev(d.rec, d.rec_cap, n_act));
   a.rec = wave_out ? wave_out : d.rec;
+  SW_TRY(ensure_host(d.res_h, d.res_h_cap, 2));   // the result, then first_bad
   SW_TRY(ensure_events(d, 2));
   hipStream_t st = as_stream(opt);
   uint64_t* first_bad = reinterpret_cast<uint64_t*>(d.res_h + 1);
@@ -1308,6 +1312,7 @@ int sweep_reduce_fp(const void* payload, size_t n_elems, int dtype,
   HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fn, 256, 0));
   SW_TRY(ensure_dev(d->rec, d->rec_cap, (size_t)grid * 4));
   SW_TRY(ensure_dev(d->partials, d->partials_cap, (size_t)grid * 2));
+  SW_TRY(ensure_host(d->res_h, d->res_h_cap, 1));
   SW_TRY(ensure_events(*d, 2));
   a.partials = d->partials;
   a.rec = d->rec;

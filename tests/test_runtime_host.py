@@ -1,0 +1,91 @@
+"""The host runtime of the built library on a HIP runtime without a device
+(fake_hip.cpp): what it launches, with which pointers, and what it does when
+memory runs out."""
+import json
+import os
+import shutil
+import subprocess
+import sys
+
+import pytest
+
+from conftest import ROOT
+
+ROCM = "/opt/rocm/include"
+
+# loaded first, the stand-in serves the library's dependency of the same name
+PRELUDE = """
+import ctypes as C, json, sys
+fake = C.CDLL(sys.argv[1], mode=C.RTLD_GLOBAL)
+fake.fake_limit_pinned.argtypes = [C.c_size_t]
+fake.fake_kernel.restype = C.c_char_p
+fake.fake_arg.restype = C.c_uint64
+from paper_2608_15764_amd import ilpsweep as isw
+buf = 1 << 40
+out = {}
+def launched():
+    return [fake.fake_kernel(i).decode() for i in range(fake.fake_launches())]
+def refused(call):
+    fake.fake_reset()
+    try:
+        call()
+    except isw.SweepError as e:
+        return e.code
+    return 0
+"""
+
+
+@pytest.fixture(scope="module")
+def host(tmp_path_factory):
+    from paper_2608_15764_amd import build
+    if not shutil.which("g++") or not os.path.exists(os.path.join(ROCM, "hip")):
+        pytest.skip("no g++ or HIP headers")
+    if not os.path.exists(build.LIB):
+        pytest.skip("the library is not built")
+    fake = str(tmp_path_factory.mktemp("fake") / "libamdhip64.so.7")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__",
+                    "-Wl,-soname,libamdhip64.so.7", "-I", ROCM,
+                    os.path.join(ROOT, "tests", "fake_hip.cpp"), "-o", fake],
+                   check=True, stderr=subprocess.DEVNULL)
+
+    def run(body):
+        r = subprocess.run([sys.executable, "-c", PRELUDE + body + "\nprint(json.dumps(out))", fake],
+                           capture_output=True, text=True, cwd=ROOT, timeout=120)
+        assert r.returncode == 0, r.stderr
+        return json.loads(r.stdout.strip().split("\n")[-1])
+    return run
+
+
+def test_calls_after_a_failed_growth_have_their_results_to_write_to(host):
+    """A long sweep that cannot have pinned memory for its results gives up the
+    shorter block it had; the calls after it get one of their own, or fail too:
+    no kernel is handed an address near 0."""
+    got = host("""
+cells = isw.cell_array([isw.make_cell(buf, 1 << 20, 1, 16, 4, 1 << 16)] * 3000)
+calls = {
+    "subset": lambda: isw.sweep_xcd_subset(buf, 64 << 20, 4, 0x0F),
+    "split": lambda: isw.sweep_xcd_split(buf, 64 << 20, 4, [1.0] * 8),
+    "streams": lambda: isw.sweep_two_stream(buf, 64 << 20, 4, 2, 2, 1 << 22),
+    "sum": lambda: isw.sweep_reduce_fp(buf, 1 << 20, isw.F32, 8),
+    "cell": lambda: isw.sweep_plain(buf, 1 << 20, 1, 16, 4, 1 << 16),
+}
+for name, call in calls.items():
+    for limit in (1 << 20, 8):
+        isw.sweep_shutdown()
+        fake.fake_limit_pinned(4096)
+        isw.sweep_init(0)
+        long = refused(lambda: isw.sweep_run(cells))
+        fake.fake_limit_pinned(limit)
+        code = refused(call)
+        args = [[fake.fake_arg(i, k) for k in range(6)] for i in range(fake.fake_launches())
+                if b"finish_" in fake.fake_kernel(i)]
+        out[f"{name} {limit}"] = [long, code, launched(), args]
+""")
+    to = {"finish_xcd": (2, 3), "finish_cells": (2,), "finish_reduce": (2, 5)}
+    for name, (long, code, kernels, args) in got.items():
+        assert long == -5, name
+        if name.endswith(" 8"):
+            assert code == -5 and not kernels, (name, code, kernels)
+        else:
+            last = next(k for k in to if k in kernels[-1])
+            assert len(args) == 1 and all(args[0][k] > 4096 for k in to[last]), (name, args)
