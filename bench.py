@@ -561,7 +561,7 @@ def main():
                                               waves_list, Ks)
     # the same sweep launched eagerly, cell by cell (sweep_run): the cost of
     # one host launch per kernel against the graph replay timed above, and
-    # every kernel's own duration from the events its dispatch stamps
+    # every kernel's time from the end of the dispatch before it to its own
     arr = isw.cell_array(cells)
     isw.sweep_run(arr, raw=True)
     torch.cuda.synchronize()

@@ -150,9 +150,12 @@ typedef struct {
                                       sgprs is 0: the runtime does not report it */
   uint64_t window_ticks;   /* max(t1) - min(t0) over all waves             */
   double   window_ns;      /* window_ticks converted with the clock rate   */
-  double   event_ms;       /* hipEvent time of the kernel's dispatch: from the
-                              end of the call's previous cell, or for its
-                              first cell an event right before it          */
+  double   event_ms;       /* hipEvent time of the kernel's dispatch, from the
+                              end of the dispatch before it (the call's
+                              previous cell, or a marker that waits until
+                              the first cell is queued): the kernel and the
+                              gap in front of it, 0.1-0.7 us, and not below
+                              the 4.2 us the queue takes for a dispatch    */
   double   gbps;           /* issued_bytes / window_ns                     */
 } sweep_result_t;
 

@@ -240,6 +240,15 @@ hipError_t launch_fill(uint32_t* buf, uint64_t n_words, uint64_t seed,
 // One workgroup per cell.
 hipError_t launch_finish_cells(const FinishArgs& a, uint32_t n_cells, hipStream_t st);
 hipError_t launch_finish_xcd(const XcdFinishArgs& a, hipStream_t st);
+// One wave that leaves when `*flag` has come to `ticket`, or after `ticks` of
+// the wall clock; `done` is stamped with its end.
+struct GateArgs {
+  const uint32_t* flag;   // pinned host memory
+  uint32_t ticket;
+  uint32_t ticks;
+};
+constexpr double kGateSeconds = 200e-6;   // a host that takes longer is timed with the dispatch
+hipError_t launch_gate(const GateArgs& a, hipStream_t st, hipEvent_t done);
 hipError_t launch_read_clock(uint64_t* out, hipStream_t st);
 // 16-byte loads of a lane's group: 8 at one wave per SIMD, 4 above, so that
 // at least 8 MiB can be in flight at every occupancy of the default grid.

@@ -1,5 +1,7 @@
 // Buffer fill, per-cell finishing, clock probe and the precision variant's
 // streaming FP reduction.
+#include <hip/hip_ext.h>
+
 #include "device.hpp"
 #include "kernels.hpp"
 
@@ -227,6 +229,24 @@ __global__ void read_clock(uint64_t* out) {
 hipError_t launch_read_clock(uint64_t* out, hipStream_t st) {
   hipLaunchKernelGGL(read_clock, dim3(1), dim3(64), 0, st, out);
   return hipGetLastError();
+}
+
+// ------------------------------------------------------------------ gate
+// Tickets count up and wrap: one that has been passed stays passed, also where
+// a later call's flag is already up when this wave starts.  Every wait ends
+// after a.ticks of the clock.
+__global__ void gate(GateArgs a) {
+  const uint64_t t0 = wall_ticks();
+  while ((int32_t)(__hip_atomic_load(a.flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) -
+                   a.ticket) < 0 &&
+         wall_ticks() - t0 < a.ticks) {
+  }
+}
+
+hipError_t launch_gate(const GateArgs& a, hipStream_t st, hipEvent_t done) {
+  void* args[] = {const_cast<GateArgs*>(&a)};
+  return hipExtLaunchKernel(reinterpret_cast<const void*>(&gate), dim3(1), dim3(1), args, 0, st,
+                            nullptr, done, 0);
 }
 
 // --------------------------------------------------- precision reduction

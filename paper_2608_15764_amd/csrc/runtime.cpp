@@ -65,7 +65,9 @@ struct Dev {
   uint64_t* walk_out = nullptr;   // 4 words per walker
   uint64_t* offs_h = nullptr;   // per-cell record offsets, pinned: the finish reads them
   size_t offs_h_cap = 0;
-  hipEvent_t start = nullptr;   // recorded before a call's first timed dispatch
+  hipEvent_t start = nullptr;   // the end of the gate before a call's first timed dispatch
+  uint32_t* gate = nullptr;     // pinned: tickets up to this one may pass
+  uint32_t ticket = 0;          // the last gate's
   std::vector<hipEvent_t> ev;
   hipStream_t capture = nullptr;
   // kernel attributes and residency limit per (kernel, WG threads, LDS)
@@ -115,10 +117,8 @@ int ensure_host(T*& p, size_t& cap, size_t n) {
   return SWEEP_OK;
 }
 
-// The start event only marks a time, so it needs no fence to the host
-// (1.3 us of a single call).
 int ensure_events(Dev& d, size_t n) {
-  if (!d.start) HIP_TRY(hipEventCreateWithFlags(&d.start, hipEventDisableSystemFence));
+  if (!d.start) HIP_TRY(hipEventCreate(&d.start));
   while (d.ev.size() < n) {
     hipEvent_t e;
     HIP_TRY(hipEventCreate(&e));
@@ -134,6 +134,7 @@ void release_device(Dev* d) {
   if (d->partials) (void)hipFree(d->partials);
   if (d->spare) (void)hipHostFree(d->spare);
   if (d->dsum_h) (void)hipHostFree(d->dsum_h);
+  if (d->gate) (void)hipHostFree(d->gate);
   if (d->clk) (void)hipFree(d->clk);
   if (d->chase_out) (void)hipFree(d->chase_out);
   if (d->walk_out) (void)hipFree(d->walk_out);
@@ -149,8 +150,10 @@ int setup_device(Dev* d) {
   // scratch for the largest default grid (32 waves per CU)
   SW_TRY(ensure_dev(d->rec, d->rec_cap, (size_t)d->num_cus * 32));
   SW_TRY(ensure_host(d->res_h, d->res_h_cap, 64));
-  size_t one_h = 0, clk_cap = 0;
+  size_t one_h = 0, one_g = 0, clk_cap = 0;
   SW_TRY(ensure_host(d->dsum_h, one_h, 1));
+  SW_TRY(ensure_host(d->gate, one_g, 1));
+  *d->gate = d->ticket;
   SW_TRY(ensure_dev(d->clk, clk_cap, 1));
   size_t chase_cap = 0;
   SW_TRY(ensure_dev(d->chase_out, chase_cap, 5));
@@ -283,31 +286,47 @@ int prepare(Dev& d, const sweep_cell_t& c, int pin, Prepared* out, bool cache = 
 
 // Launches kernel `fn` whose one parameter is the struct `a`.  With `stop`,
 // hipExtLaunchKernel stamps it from the dispatch's own end.  A dispatch is
-// timed from the event before it in the stream: the end of the previous
-// timed dispatch, or for a call's first one `start`, recorded here.  (Asking
-// hipExtLaunchKernel for a start event as well costs a single call 13 us and
-// every dispatch of a sweep a gap of 5 us or more, since it stops the queue
-// around the kernel; the times agree to 0.1 us for a single dispatch, and
-// back to back they include the gap between two dispatches, 0.1-0.7 us:
-// 17.56 us stamped by itself, 17.64 from an event before it, 18.22 from the
-// end of the dispatch before it.)
+// timed from the end of the dispatch before it in the stream: the previous
+// timed one, or for a call's first one (`first`) that of the gate, a wave that
+// waits until the dispatch behind it is in the queue, so that the time holds
+// no wait for the host.
+//
+// Asking hipExtLaunchKernel for a start event as well gives the same times
+// (64 MiB read in 11.4 us behind the gate, 11.4 to 12.4 stamped by itself; 256
+// MiB 42.0 against 42.2 to 43.2), but stops the queue around the kernel: a
+// single call takes 15 us more and every dispatch of a sweep 5 us or more.  An
+// event recorded in front of the first dispatch ends before the host has
+// sent that one: 17.2 and 47.9 us.  The gate costs a 4 MiB call 3 us over
+// such an event (22.5 against 19.6), a 64 MiB one nothing.
+//
+// Back to back the times include the gap between two dispatches, 0.1-0.7 us
+// (32 cells of 64 MiB, 11.2 against 10.7 us each), and none is below the 4.2
+// us that the queue takes for a dispatch with an event.  Cells that short are
+// not timed with the host either: runs of 8 and 28 cells of 1 to 16 MiB read
+// 4.18 us a cell with every cell queued before the first one starts, 4.20 as
+// they come.
 template <class Args>
 hipError_t launch_timed(const void* fn, uint32_t grid, uint32_t threads, size_t lds,
-                        hipStream_t st, const Args& a, hipEvent_t start, hipEvent_t stop) {
+                        hipStream_t st, const Args& a, Dev* first, hipEvent_t stop) {
   void* args[] = {const_cast<Args*>(&a)};
-  if (start) {
-    const hipError_t e = hipEventRecord(start, st);
+  if (first) {
+    // the wall clock's nominal rate is ticks per second
+    const GateArgs g{first->gate, ++first->ticket, (uint32_t)(first->nominal_hz * kGateSeconds)};
+    const hipError_t e = launch_gate(g, st, first->start);
     if (e != hipSuccess) return e;
   }
-  if (stop)
-    return hipExtLaunchKernel(fn, dim3(grid), dim3(threads), args, lds, st, nullptr, stop, 0);
-  return hipLaunchKernel(fn, dim3(grid), dim3(threads), args, lds, st);
+  const hipError_t e =
+      stop ? hipExtLaunchKernel(fn, dim3(grid), dim3(threads), args, lds, st, nullptr, stop, 0)
+           : hipLaunchKernel(fn, dim3(grid), dim3(threads), args, lds, st);
+  // sent, or not to be: the gate's wave may leave
+  if (first) __atomic_store_n(first->gate, first->ticket, __ATOMIC_RELEASE);
+  return e;
 }
 
 // Launches the cell's kernel; the wave records go to `rec`, which holds at
 // least the cell's waves.
 hipError_t enqueue(const Prepared& p, hipStream_t st, sweep_wave_rec_t* rec,
-                   uint32_t* lane_out, hipEvent_t start, hipEvent_t stop) {
+                   uint32_t* lane_out, Dev* first, hipEvent_t stop) {
   const sweep_plan_t& o = p.plan.pub;
   const uint64_t V = (uint64_t)p.c.vec_width;
   if (p.c.kind == SWEEP_KIND_PLAIN) {
@@ -324,7 +343,7 @@ hipError_t enqueue(const Prepared& p, hipStream_t st, sweep_wave_rec_t* rec,
     a.extra = (uint32_t)(o.Q % o.waves);
     a.gstep = p.plan.gstep * V;
     a.jstep = p.plan.jstep * V;
-    return launch_timed(p.fn, p.grid, p.threads, p.lds, st, a, start, stop);
+    return launch_timed(p.fn, p.grid, p.threads, p.lds, st, a, first, stop);
   }
   LdsArgs a;
   a.buf = static_cast<const uint8_t*>(p.c.buf);
@@ -335,7 +354,7 @@ hipError_t enqueue(const Prepared& p, hipStream_t st, sweep_wave_rec_t* rec,
   a.iters = (uint32_t)(o.Q / o.waves);
   a.extra = (uint32_t)(o.Q % o.waves);
   a.waves = p.plan.wg_waves;
-  return launch_timed(p.fn, p.grid, p.threads, p.lds, st, a, start, stop);
+  return launch_timed(p.fn, p.grid, p.threads, p.lds, st, a, first, stop);
 }
 
 std::vector<uint64_t> record_offsets(const std::vector<Prepared>& ps) {
@@ -447,7 +466,7 @@ int run_prepared(Dev& d, std::vector<Prepared>& ps, hipStream_t st,
   FinishArgs fin;
   SW_TRY(finish_args(d, rec, offs, &fin));
   for (size_t i = 0; i < n; ++i)
-    HIP_TRY(enqueue(ps[i], st, rec + offs[i], lane_out, i == 0 ? d.start : nullptr, d.ev[i]));
+    HIP_TRY(enqueue(ps[i], st, rec + offs[i], lane_out, i == 0 ? &d : nullptr, d.ev[i]));
   HIP_TRY(launch_finish_cells(fin, (uint32_t)n, st));
   HIP_TRY(hipEventRecord(d.ev[n], st));
   HIP_TRY(hipEventSynchronize(d.ev[n]));
@@ -542,7 +561,7 @@ int xcd_run(Dev& d, const sweep_opts_t* opt, Prepared& p, uint64_t n_act, Args& 
   const XcdFinishArgs fin{a.rec, n_act, d.res_h, first_bad, run,
                           (uint32_t)__builtin_popcount(mask), xcd_list(mask)};
   HIP_TRY(launch_clear_records(a.rec, n_act, st));
-  HIP_TRY(launch_timed(p.fn, p.grid, p.threads, p.lds, st, a, d.start, d.ev[0]));
+  HIP_TRY(launch_timed(p.fn, p.grid, p.threads, p.lds, st, a, &d, d.ev[0]));
   HIP_TRY(launch_finish_xcd(fin, st));
   HIP_TRY(hipEventRecord(d.ev[1], st));
   HIP_TRY(hipEventSynchronize(d.ev[1]));
@@ -659,7 +678,7 @@ int two_stream_impl(const void* buf, size_t bytes, int depth, int waves_plain,
   hipStream_t st = as_stream(opt);
   FinishArgs fin;
   SW_TRY(finish_args(*d, rec, {0ull, (uint64_t)wa, (uint64_t)wa + wb}, &fin));
-  HIP_TRY(launch_timed(fn, grid, threads, lds, st, a, d->start, d->ev[0]));
+  HIP_TRY(launch_timed(fn, grid, threads, lds, st, a, d, d->ev[0]));
   HIP_TRY(launch_finish_cells(fin, 2, st));
   HIP_TRY(hipEventRecord(d->ev[1], st));
   HIP_TRY(hipEventSynchronize(d->ev[1]));
@@ -1317,7 +1336,7 @@ int sweep_reduce_fp(const void* payload, size_t n_elems, int dtype,
   a.partials = d->partials;
   a.rec = d->rec;
   hipStream_t st = as_stream(opt);
-  HIP_TRY(launch_timed(fn, grid, 256u, 0, st, a, d->start, d->ev[0]));
+  HIP_TRY(launch_timed(fn, grid, 256u, 0, st, a, d, d->ev[0]));
   HIP_TRY(launch_finish_reduce(ReduceFinishArgs{d->partials, grid, d->dsum_h, d->rec,
                                                 (uint64_t)grid * 4, d->res_h},
                                st));

@@ -562,6 +562,7 @@ def batched_autotuned(n_points=64, n=10, default=(16, 2, 16, isw.CACHE_BYPASS_L1
     # point alone in its graph node
     hbm_bytes = sum(pts[i]["issued_bytes"] for i in hbm)
     hbm_ns = sum(_median([r[i]["window_ns"] for r in u_runs]) for i in hbm)
+    # (each event time holds the gap in front of its dispatch)
     plain_ms = _median([sum(r["event_ms"] for r in run) for run in p_runs])
     out = {
         "sizes": len(sizes),

@@ -15,6 +15,7 @@ namespace {
 struct Launch {
   std::string kernel;
   uint64_t args[8];           // the head of the kernel's argument struct
+  void *start, *stop;         // the events that it was launched with
 };
 struct Event {
   unsigned flags;
@@ -23,7 +24,8 @@ struct Event {
 std::map<const void*, std::string> g_names;
 std::vector<Launch> g_launches;
 size_t g_pinned = SIZE_MAX;   // an allocation of more pinned bytes fails
-unsigned g_start_flags = 0;   // of the last interval's start event
+int g_fail = -1;              // the launch that fails, counted from the last reset
+std::vector<void*> g_from;    // start events of the intervals asked for
 dim3 g_grid, g_block;
 size_t g_lds = 0;
 hipStream_t g_stream = nullptr;
@@ -33,14 +35,17 @@ hipError_t allocate(void** p, size_t n) {
   return hipSuccess;
 }
 
-hipError_t launch(const void* fn, void** args) {
+hipError_t launch(const void* fn, void** args, void* start = nullptr, void* stop = nullptr) {
   Launch l;
   l.kernel = g_names.at(fn);
+  l.start = start;
+  l.stop = stop;
   std::memset(l.args, 0, sizeof(l.args));
-  // the finishing kernels' structs, whose pointers the tests look at
+  // the structs whose pointers the tests look at
   if (l.kernel.find("finish_") != std::string::npos) std::memcpy(l.args, args[0], 48);
+  if (l.kernel.find("gate") != std::string::npos) std::memcpy(l.args, args[0], 16);
   g_launches.push_back(l);
-  return hipSuccess;
+  return (int)g_launches.size() - 1 == g_fail ? hipErrorLaunchFailure : hipSuccess;
 }
 
 }  // namespace
@@ -48,12 +53,22 @@ hipError_t launch(const void* fn, void** args) {
 extern "C" {
 
 // ---- the tests' side
-void fake_reset() { g_launches.clear(); }
+void fake_reset() {
+  g_launches.clear();
+  g_from.clear();
+  g_fail = -1;
+}
+void fake_fail_launch(int i) { g_fail = i; }
 void fake_limit_pinned(size_t bytes) { g_pinned = bytes; }
 int fake_launches() { return (int)g_launches.size(); }
 const char* fake_kernel(int i) { return g_launches[(size_t)i].kernel.c_str(); }
 uint64_t fake_arg(int i, int k) { return g_launches[(size_t)i].args[k]; }
-unsigned fake_start_flags() { return g_start_flags; }
+// Which launch ended with the event that interval i was measured from, or -1.
+int fake_interval_from(int i) {
+  for (size_t k = 0; (size_t)i < g_from.size() && k < g_launches.size(); ++k)
+    if (g_launches[k].stop && g_launches[k].stop == g_from[(size_t)i]) return (int)k;
+  return -1;
+}
 
 // ---- registration and launches
 void** __hipRegisterFatBinary(const void*) {
@@ -84,8 +99,8 @@ hipError_t hipLaunchKernel(const void* fn, dim3, dim3, void** args, size_t, hipS
   return launch(fn, args);
 }
 hipError_t hipExtLaunchKernel(const void* fn, dim3, dim3, void** args, size_t, hipStream_t,
-                              hipEvent_t, hipEvent_t, int) {
-  return launch(fn, args);
+                              hipEvent_t start, hipEvent_t stop, int) {
+  return launch(fn, args, start, stop);
 }
 hipError_t hipFuncGetAttributes(hipFuncAttributes* a, const void*) {
   std::memset(a, 0, sizeof(*a));
@@ -161,7 +176,7 @@ hipError_t hipEventDestroy(hipEvent_t e) {
 hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
 hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
 hipError_t hipEventElapsedTime(float* ms, hipEvent_t start, hipEvent_t) {
-  g_start_flags = reinterpret_cast<Event*>(start)->flags;
+  g_from.push_back(start);
   *ms = 1.0f;
   return hipSuccess;
 }

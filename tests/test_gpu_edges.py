@@ -331,3 +331,25 @@ def test_strided_plain_forms(nbytes, K, w, policy):
     s, x = _prefix_sinks(words, nbytes // 4)
     assert r["issued_loads"] == L
     assert (r["sum32"], r["xor32"]) == ((K * s) & 0xFFFFFFFF, x if K & 1 else 0)
+
+
+@pytest.mark.parametrize("entry", ["plain", "lds", "streams", "subset", "sum"])
+def test_event_time_of_a_single_call_holds_no_host_time(entry):
+    """The event time of a call's only dispatch is its clock window and the
+    start and end of a dispatch, which take about 1 us of a kernel longer than
+    the 4.2 us floor; the host needs 4 us more from a marker to a launch."""
+    nbytes = 256 << 20
+    buf = dev_bytes(nbytes)
+    isw.sweep_fill_u32(buf, nbytes, SEED + 12)
+    n = nbytes // 16
+    call = {"plain": lambda: [isw.sweep_plain(buf, nbytes, 4, 16, 16, n)],
+            "lds": lambda: [isw.sweep_lds_async(buf, nbytes, 8, 16, 4, n)],
+            "streams": lambda: isw.sweep_two_stream(buf, nbytes, 8, 4, 4, n),
+            "subset": lambda: [isw.sweep_xcd_subset(buf, nbytes, 8, 0xFF)],
+            "sum": lambda: [isw.sweep_reduce_fp(buf.zero_(), nbytes // 4, isw.F32, 16)[1]]}[entry]
+    print("event time", entry, flush=True)
+    over = []
+    for _ in range(40):
+        rs = call()
+        over.append(rs[0]["event_ms"] * 1e3 - max(r["window_ns"] for r in rs) * 1e-3)
+    assert 0 < float(np.median(over[8:])) < 2.5, sorted(over)

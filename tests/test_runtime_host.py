@@ -89,3 +89,47 @@ for name, call in calls.items():
         else:
             last = next(k for k in to if k in kernels[-1])
             assert len(args) == 1 and all(args[0][k] > 4096 for k in to[last]), (name, args)
+
+
+def test_timed_dispatches_run_from_the_end_of_the_one_before(host):
+    """The first timed dispatch of a call is timed from the end of a gate that
+    waits for its submission, the next ones from each other; the gate's flag is
+    up when the call returns, also where the dispatch fails to launch."""
+    got = host("""
+cells = isw.cell_array([isw.make_cell(buf, 1 << 20, K, 16, 4, 1 << 16) for K in (1, 2, 3)])
+calls = {
+    "run": lambda: isw.sweep_run(cells),
+    "plain": lambda: isw.sweep_plain(buf, 1 << 20, 1, 16, 4, 1 << 16),
+    "subset": lambda: isw.sweep_xcd_subset(buf, 64 << 20, 4, 0x0F),
+    "split": lambda: isw.sweep_xcd_split(buf, 64 << 20, 4, [1.0] * 8),
+    "streams": lambda: isw.sweep_two_stream(buf, 64 << 20, 4, 2, 2, 1 << 22),
+    "sum": lambda: isw.sweep_reduce_fp(buf, 1 << 20, isw.F32, 8),
+}
+isw.sweep_init(0)
+def gate():
+    at = [i for i, k in enumerate(launched()) if "gate" in k]
+    i = at[0]
+    flag = C.c_uint32.from_address(fake.fake_arg(i, 0)).value
+    return at, flag, fake.fake_arg(i, 1) & 0xFFFFFFFF, fake.fake_arg(i, 1) >> 32
+for name, call in calls.items():
+    code = refused(call)
+    at, flag, ticket, ticks = gate()
+    n = {"run": 3, "subset": 0, "split": 0}.get(name, 1)
+    froms = [fake.fake_interval_from(i) for i in range(n)]
+    fake.fake_reset()
+    fake.fake_fail_launch(at[0] + 1)
+    try:
+        call()
+        failed = 0
+    except isw.SweepError as e:
+        failed = e.code
+    out[name] = [code, at, flag, ticket, ticks, froms, failed, gate()]
+""")
+    for name, (code, at, flag, ticket, ticks, froms, failed, after) in got.items():
+        g = at[0]
+        # (an XCD read finds no record of the wave it looks for, and says so)
+        assert code == (0 if froms else -6), (name, code)
+        assert len(at) == 1 and flag == ticket > 0, name
+        assert froms == [g, g + 1, g + 2][:len(froms)], (name, froms)
+        assert 0 < ticks <= 100_000, (name, ticks)          # 1 ms of the 100 MHz clock at most
+        assert failed == -4 and after[1] == after[2] == ticket + 1, (name, failed, after)
