@@ -265,6 +265,11 @@ int sweep_fill_u32(void* buf, size_t bytes, uint64_t seed, void* stream);
  * before consuming any of them, then folds each 32-bit word into its sinks.
  * The grid is persistent: grid_wgs workgroups of 256 threads (4 waves), by
  * default CUs * waves_per_cu / 4, so waves_per_cu / 4 waves per SIMD.
+ * The K loads of an iteration go out back to back or 16 idle cycles apart.
+ * Which of the two depends on vec_width, the cache policy, the order, the
+ * waves a CU holds and the size, never on K: the cells of a K curve run one
+ * loop.  (12 or more waves reading more than 128 MiB in 16-byte loads are
+ * spaced, and some strided cells; the kernel's name tells.)
  *   buf        device, 16-byte aligned, read only
  *   bytes      buffer size, a multiple of 64 * vec_width
  *   K          1..16

@@ -213,11 +213,12 @@ hipError_t static_scratch(int ordinal, uint8_t** ptr);
 // ---- kernel lookup: the host launches these with their one argument
 // struct (PlainArgs, LdsArgs, TwoStreamArgs, ReduceArgs); nullptr for an
 // unknown combination.
-// plain (kernels_plain.hip), in the form for n_waves waves over `bytes`
-const void* plain_kernel(int K, int V, int policy, int order, int waves_per_cu,
-                         uint64_t n_waves, uint64_t bytes);
-// fused plain batch (kernels_fused.hip), in the form for n_waves waves;
-// `far` if a point has kFarBytes or more
+// plain (kernels_plain.hip), in the form for `resident` waves on a CU at a
+// time over `bytes`
+const void* plain_kernel(int K, int V, int policy, int order, uint64_t resident,
+                         uint64_t bytes);
+// fused plain batch (kernels_fused.hip), in the form for n_waves waves at a
+// time; `far` if a point has kFarBytes or more
 const void* fused_kernel(int K, int V, int policy, uint64_t n_waves, bool far);
 const void* xcd_kernel(int policy);
 const void* xcd_split_kernel(int policy);

@@ -118,10 +118,22 @@ namespace {
 
 typedef void (*PlainFn)(PlainArgs);
 
+// (of one load there is nothing to space)
+template <int K, int V, int POL>
+constexpr PlainFn spaced() {
+  if constexpr (K == 1) return &plain_kload<K, V, POL>;
+  else return &plain_kload_spaced<K, V, POL>;
+}
+template <int K, int V, int POL>
+constexpr PlainFn far_spaced() {
+  if constexpr (K == 1) return &plain_kload_far<K, V, POL>;
+  else return &plain_kload_far_spaced<K, V, POL>;
+}
+
 template <int V, int POL, int... Ks>
 constexpr std::array<PlainFn, 4 * sizeof...(Ks)> row(std::integer_sequence<int, Ks...>) {
-  return {&plain_kload<Ks + 1, V, POL>..., &plain_kload_spaced<Ks + 1, V, POL>...,
-          &plain_kload_far<Ks + 1, V, POL>..., &plain_kload_far_spaced<Ks + 1, V, POL>...};
+  return {&plain_kload<Ks + 1, V, POL>..., spaced<Ks + 1, V, POL>()...,
+          &plain_kload_far<Ks + 1, V, POL>..., far_spaced<Ks + 1, V, POL>()...};
 }
 
 template <int V, int POL>
@@ -139,51 +151,51 @@ const PlainFn* table(int vi, int pol) {
 
 int width_index(int V) { return V == 4 ? 0 : V == 8 ? 1 : V == 16 ? 2 : -1; }
 
-// Which form a cell takes.  K loads sent at once by many waves reach a
-// saturated HBM as bursts that some strides fold onto few channels; a gap
-// between loads spreads them, and costs what it delays elsewhere.  Measured
-// over 1 GiB, sc1 nt, GB/s back to back -> spaced:
-//  16 bytes   from 8 MiB in flight on, by 8 or more waves per CU or in groups
-//             of 16 KiB, over a buffer that the 256 MiB last-level cache does
-//             not hold: 16 waves, K = 8 6390 -> 6950, K = 16 5960 -> 6840; 32
-//             waves, K = 8 6680 -> 6980; 4 waves, K = 16 6660 -> 6880; most
-//             others within 1 %.  Not 4 waves, K = 4 6150 -> 5590, K = 12
-//             6890 -> 6680; 64 MiB, 4 waves, K = 16 6840 -> 6260.  At 192 MiB
-//             the two are level.
-//  4, 8 bytes between 8 and 14 MiB in flight, 4 bytes from 16 waves per CU on,
-//             8 from 8; 8 bytes, 16 waves, K = 6 6600 -> 7240, 28 waves, K = 3
-//             6160 -> 6930; 4 bytes, 24 waves, K = 8 6120 -> 6890; over 64 to
-//             128 MiB the same (28 waves, K = 3 5900 -> 6600).  Not above: 24
-//             waves, K = 5 of 8 bytes (15 MiB) 7140 -> 6730, K = 10 of 4 over
-//             20 MiB 6950 -> 6780; not below: 4 waves, K = 16 of 8 bytes (8
-//             MiB) 7260 -> 6260; 12 waves, K = 12 of 4 bytes 6970 -> 6180.
-//  strided, 16 bytes, past the L1: the loads of a group may all fall on one
-//             segment of a buffer read more than once, and then miss together
-//             where spaced ones hit: above 14 MiB in flight, and from 8 MiB on
-//             over 64 MiB and more; 4 MiB, 8 waves, K = 8 16600 -> 19360, K =
-//             16 17000 -> 21000; 16 MiB, 16 waves, K = 4 12120 -> 13780; 128
-//             MiB, 4 waves, K = 8 5250 -> 5650.  Below, 4 MiB, 8 waves, K = 3
-//             11020 -> 9750.
-// Gaps of 4 and 8 cycles lift the same cells less.
-bool spaced_form(int K, int V, int policy, int order, int waves_per_cu, uint64_t n_waves,
-                 uint64_t bytes) {
-  const uint64_t group = (uint64_t)K * kWave * V, in_flight = n_waves * group;
-  if (V == 16 && order == SWEEP_ORDER_STRIDED && policy >= SWEEP_CACHE_BYPASS_L1 &&
-      (in_flight > (14ull << 20) || (in_flight >= (8ull << 20) && bytes >= (64ull << 20))))
-    return true;
-  if (in_flight <= (8ull << 20)) return false;
+// Which form a cell takes: a rule on everything but K, so that the loop is one
+// and the same along a K curve (a single load has no gap in either form).
+// K loads sent at once by many waves reach a saturated HBM as bursts that some
+// strides fold onto few channels; a gap between loads spreads them, and costs
+// what it delays elsewhere.  So each form wins at some K and loses at others,
+// and the line is drawn on the mean over K = 2..16 of ln(time back to back /
+// time spaced), in percent, here under the default / nt / sc1 / sc1 nt policy
+// with [the least, the most] of the cells:
+//  16 bytes, round robin and blocked, from 12 waves per CU on over more than the
+//             last-level cache keeps: 256 MiB, 12 waves +0.8 / +0.1 / +0.5 / +0.1
+//             [-6 +7], 20 waves +1.0 / +0.1 / +0.8 / +0.8 [-7 +11]; 1 GiB, 12
+//             waves +0.5 / 0.0 / +0.9 / +0.1 [-3 +4], 16 waves +0.5 / +0.2 / +0.6
+//             / +0.2 [-5 +11]; 4 GiB, 16 waves +0.1 / 0.0 / +0.2 / -0.2 [-3 +8].
+//             Not below: 1 GiB, 8 waves +0.6 / -0.1 / 0.0 / 0.0 [-8 +6], 4
+//             waves -3.0 / -3.5 / -2.8 / -3.6 [-15 +8]; 64 MiB, 12 waves +0.5 /
+//             -0.2 / +0.4 / -0.2 [-9 +5].
+//  16 bytes, strided, under any policy but the default, from 12 waves on over
+//             one XCD's 4 MiB L2: the loads of a group may all fall on one
+//             segment and then miss together where spaced ones hit.  12 waves
+//             +0.1 / +1.8 / +2.3 / +1.3 [-8 +17], 28 waves -0.2 / +2.4 / +1.8 /
+//             +3.0 [-7 +13].  Not over 16 MiB, 20 waves -0.5 / -0.8 / +0.7 /
+//             +0.2 [-16 +11], nor 160 MiB, 28 waves -2.6 / -2.8 / -2.6 / -2.3.
+//  4, 8 bytes, strided, at 32 waves over 256 MiB and more: 8 bytes, 256 MiB
+//             +2.5 / +1.3 / +2.7 / +1.3 [-2 +10], 4 GiB +2.7 / +4.4 / +3.0 / +4.1
+//             [-7 +13]; 4 bytes, 1 GiB +3.1 / +2.8 / +0.3 / -0.3 [-8 +10].  Not
+//             at 24 waves: 256 MiB, 8 bytes -1.5 / -1.7 / -1.5 / -1.8, 4 bytes
+//             -0.1 / -1.5 / -2.2 / -2.2.
+//  4, 8 bytes, other orders: never.  1 GiB, 8 bytes, 16 waves -0.1 / -1.1 / 0.0 /
+//             -0.8 [-7 +10], 4 bytes, 8 waves -10.5 / -14.2 / -11.0 / -15.1.
+// `resident` is the waves of the launch that a CU holds at a time.
+bool spaced_form(int V, int policy, int order, uint64_t resident, uint64_t bytes) {
+  if (order != SWEEP_ORDER_STRIDED)
+    return V == 16 && resident >= 12 && bytes > (128ull << 20);
   if (V == 16)
-    return bytes > (128ull << 20) && (waves_per_cu >= 8 || group >= (16ull << 10));
-  return in_flight <= (14ull << 20) && bytes >= (64ull << 20) && waves_per_cu * V >= 64;
+    return policy != SWEEP_CACHE_DEFAULT && resident >= 12 && bytes <= (4ull << 20);
+  return resident >= 32 && bytes >= (256ull << 20);
 }
 
 }  // namespace
 
-const void* plain_kernel(int K, int V, int policy, int order, int waves_per_cu,
-                         uint64_t n_waves, uint64_t bytes) {
+const void* plain_kernel(int K, int V, int policy, int order, uint64_t resident,
+                         uint64_t bytes) {
   const int vi = width_index(V);
   if (vi < 0 || K < 1 || K > kMaxK || policy < 0 || policy >= kNumPolicies) return nullptr;
-  const bool spaced = spaced_form(K, V, policy, order, waves_per_cu, n_waves, bytes);
+  const bool spaced = spaced_form(V, policy, order, resident, bytes);
   const bool far = bytes >= kFarBytes;
   return reinterpret_cast<const void*>(table(vi, policy)[(2 * far + spaced) * kMaxK + K - 1]);
 }

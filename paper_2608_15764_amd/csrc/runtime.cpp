@@ -249,10 +249,12 @@ int prepare(Dev& d, const sweep_cell_t& c, int pin, Prepared* out, bool cache = 
     return fail(SWEEP_EALIGN, "buffer must be 16-byte aligned");
   if (c.cache_policy < 0 || c.cache_policy > 3)
     return fail(SWEEP_EINVAL, "unknown cache policy");
-  const bool far = c.bytes >= kFarBytes;
-  p.fn = c.kind == SWEEP_KIND_PLAIN ? plain_kernel(c.K, c.vec_width, c.cache_policy,
-                                               c.order, c.waves_per_cu, p.plan.pub.waves, c.bytes)
-                                    : lds_kernel(c.kind, c.K, c.cache_policy, far);
+  // a grid of several turns has no more waves in flight than the CUs hold
+  const uint64_t resident =
+      std::min<uint64_t>(p.plan.pub.waves / d.num_cus, pin ? (uint64_t)c.waves_per_cu : 32u);
+  p.fn = c.kind == SWEEP_KIND_PLAIN
+             ? plain_kernel(c.K, c.vec_width, c.cache_policy, c.order, resident, c.bytes)
+             : lds_kernel(c.kind, c.K, c.cache_policy, c.bytes >= kFarBytes);
   if (!p.fn) return fail(SWEEP_EINVAL, "no kernel for this cell");
   p.grid = p.plan.pub.grid_wgs;
   p.threads = p.plan.pub.wg_threads;

@@ -353,3 +353,34 @@ def test_event_time_of_a_single_call_holds_no_host_time(entry):
         rs = call()
         over.append(rs[0]["event_ms"] * 1e3 - max(r["window_ns"] for r in rs) * 1e-3)
     assert 0 < float(np.median(over[8:])) < 2.5, sorted(over)
+
+
+@pytest.mark.parametrize("policy", [0, 1, 2, 3])
+@pytest.mark.parametrize("V,order,w,nbytes", [
+    (16, 0, 8, (128 << 20) + 1024), (16, 0, 12, 128 << 20), (16, 1, 12, (128 << 20) + 1024),
+    (16, 2, 8, 4 << 20), (16, 2, 12, 4 << 20), (16, 2, 28, (4 << 20) + 1024),
+    (16, 2, 16, (64 << 20) - 1024), (8, 2, 28, 256 << 20), (8, 2, 32, 256 << 20),
+    (4, 2, 32, (256 << 20) - 512), (4, 2, 32, 256 << 20),
+    (4, 2, 32, (1 << 32) + 512), (8, 2, 32, (1 << 32) + 1024), (16, 1, 32, (1 << 32) + 1024)])
+def test_plain_forms_on_both_sides_of_every_line(V, order, w, nbytes, policy):
+    """The forms of the plain loop at the lines in waves, order and size where
+    the choice changes, under every policy and both walks, at a small and a
+    large K: a pass and a bit, so that groups wrap, and in strided cells a step
+    between the loads of a group that is no whole turn of the buffer."""
+    buf = dev_bytes(nbytes)
+    isw.sweep_fill_u32(buf, nbytes, SEED + 13)
+    words = buf.view(torch.int32)
+    whole = _prefix_sinks(words, nbytes // 4)
+    n_vec = nbytes // V
+    for K in (2, 13):
+        L = n_vec + 64 * K * 1000 + 77
+        Q = L // (64 * K)
+        assert Q * 64 % n_vec                       # the strided step between two loads
+        print("plain form", V, "order", order, w, nbytes, "policy", policy, "K", K, flush=True)
+        r = isw.sweep_plain(buf, nbytes, K, V, w, L,
+                            isw.make_opts(cache_policy=policy, order=order))
+        turns, rest = divmod(64 * K * Q, n_vec)
+        more = _prefix_sinks(words, rest * V // 4)
+        assert r["issued_loads"] == 64 * K * Q
+        assert (r["sum32"], r["xor32"]) == ((turns * whole[0] + more[0]) & 0xFFFFFFFF,
+                                            (whole[1] if turns & 1 else 0) ^ more[1])

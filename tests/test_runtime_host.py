@@ -133,3 +133,37 @@ for name, call in calls.items():
         assert froms == [g, g + 1, g + 2][:len(froms)], (name, froms)
         assert 0 < ticks <= 100_000, (name, ticks)          # 1 ms of the 100 MHz clock at most
         assert failed == -4 and after[1] == after[2] == ticket + 1, (name, failed, after)
+
+
+def test_the_plain_loop_is_one_along_a_K_curve(host):
+    """Which form of the plain loop runs depends on nothing that a K curve
+    varies: the cells of a curve run one kernel but for its K (of one load the
+    forms are the same).  A grid of several turns takes the form of one."""
+    got = host("""
+MIB = 1 << 20
+for V in (4, 8, 16):
+    for w in range(4, 33, 4):
+        for mib in (1, 4, 5, 64, 65, 128, 129, 256, 1024, 5120):
+            for order in range(3):
+                for policy in range(4):
+                    def cells(turns):
+                        wgs = 256 * w // 4 * turns if turns else 0
+                        return [isw.make_cell(buf, mib * MIB, K, V, w, mib * MIB // V * 16,
+                                              cache_policy=policy, order=order, grid_wgs=wgs)
+                                for K in range(1, 17)]
+                    for turns in (0, 3):
+                        fake.fake_reset()
+                        isw.sweep_run(cells(turns))
+                        ran = [k for k in launched() if "plain_kload" in k]
+                        forms = [k[:k.index("ILi")] for k in ran]
+                        out[f"{V} {w} {mib} {order} {policy} {turns}"] = [
+                            len(ran), sorted(set(forms[1:])), forms[0]]
+""")
+    spaced = 0
+    for case, (n, forms, first) in got.items():
+        assert n == 16 and len(forms) == 1, (case, forms)
+        assert "spaced" not in first and ("far" in first) == (" 5120 " in case), (case, first)
+        assert ("far" in first) == ("far" in forms[0]), (case, first, forms)
+        assert got[case[:-1] + "0"][1] == forms, case
+        spaced += "spaced" in forms[0]
+    assert 0 < spaced < len(got)
