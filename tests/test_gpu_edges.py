@@ -384,3 +384,21 @@ def test_plain_forms_on_both_sides_of_every_line(V, order, w, nbytes, policy):
         assert r["issued_loads"] == 64 * K * Q
         assert (r["sum32"], r["xor32"]) == ((turns * whole[0] + more[0]) & 0xFFFFFFFF,
                                             (whole[1] if turns & 1 else 0) ^ more[1])
+
+
+@pytest.mark.parametrize("policy", [0, 1, 2, 3])
+@pytest.mark.parametrize("nbytes,K,w", [(4 << 20, 8, 8), (4 << 20, 15, 8), (4 << 20, 16, 16),
+                                        (1 << 20, 16, 24), ((4 << 20) + 1024, 16, 24)])
+def test_strided_groups_that_wrap_between_their_loads(nbytes, K, w, policy):
+    """Strided 16-byte cells that read a small buffer many times, with a step
+    between the loads of a group that wraps and is no whole turn."""
+    buf = dev_bytes(nbytes)
+    isw.sweep_fill_u32(buf, nbytes, SEED + 14)
+    segs = nbytes // 1024
+    Q = segs + segs // 3 + 1
+    print("strided wrap", nbytes, K, w, "policy", policy, flush=True)
+    r = isw.sweep_plain(buf, nbytes, K, 16, w, 64 * K * Q,
+                        isw.make_opts(cache_policy=policy, order=2))
+    assert Q % segs and r["issued_loads"] == 64 * K * Q
+    assert (r["sum32"], r["xor32"]) == _wrapped_sinks(buf.view(torch.int32), nbytes // 16,
+                                                      64 * K * Q)
