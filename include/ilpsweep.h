@@ -134,7 +134,10 @@ typedef struct {
                               fixed-work, round-robin cells that share K,
                               vector width, cache policy and launch shape as
                               one persistent launch over their concatenated
-                              wave-groups (results per cell as before) */
+                              wave-groups (results per cell as before).
+                              Its loop has two forms, chosen by the bytes in
+                              flight, K among them: a K curve is for cells
+                              of their own                                  */
 } sweep_opts_t;
 
 typedef struct {

@@ -55,7 +55,9 @@ __device__ __forceinline__ PointRegs point_regs(const uint8_t* base, const Fused
 // 2645 us with nt loads, 2620 against 2642 with sc1 nt; K = 4 at 16 (16 MiB)
 // 880 against 895 us for 5.5 GiB.  Below that back to back is faster: K = 3 of
 // 8 bytes at 8 waves (3 MiB), 24 points of 4 to 16 MiB, 69 against 64 us; K =
-// 3 of 16 bytes at 8 waves (6 MiB) 2680 against 2640 us for the 17.5 GiB.
+// 3 of 16 bytes at 8 waves (6 MiB) 2680 against 2640 us for the 17.5 GiB.  (The
+// choice depends on K, as a plain cell's must not: neighbouring points share
+// the launch, so their windows are no K curve.)
 template <int K, int V, int POL>
 __global__ __launch_bounds__(kPlainWgThreads) void fused_kload(FusedArgs a) {
   const uint32_t lane = lane_id();
@@ -175,7 +177,8 @@ hipError_t launch_clear_records(sweep_wave_rec_t* rec, uint64_t n, hipStream_t s
 
 namespace {
 
-// Bytes in flight up to which a group's loads go out back to back.
+// Bytes in flight, of the waves that run at a time, up to which a group's loads
+// go out back to back.
 constexpr uint64_t kAheadBytes = 6ull << 20;
 
 typedef void (*FusedFn)(FusedArgs);

@@ -218,6 +218,7 @@ struct Prepared {
   uint32_t grid = 0, threads = 0;
   size_t lds = 0;
   int max_wgs = 0;
+  uint64_t at_a_time = 0;   // waves that the CUs hold together
   hipFuncAttributes fa{};
 };
 
@@ -250,10 +251,11 @@ int prepare(Dev& d, const sweep_cell_t& c, int pin, Prepared* out, bool cache = 
   if (c.cache_policy < 0 || c.cache_policy > 3)
     return fail(SWEEP_EINVAL, "unknown cache policy");
   // a grid of several turns has no more waves in flight than the CUs hold
-  const uint64_t resident =
-      std::min<uint64_t>(p.plan.pub.waves / d.num_cus, pin ? (uint64_t)c.waves_per_cu : 32u);
+  p.at_a_time = std::min<uint64_t>(p.plan.pub.waves,
+                                   (uint64_t)d.num_cus * (pin ? (uint32_t)c.waves_per_cu : 32u));
   p.fn = c.kind == SWEEP_KIND_PLAIN
-             ? plain_kernel(c.K, c.vec_width, c.cache_policy, c.order, resident, c.bytes)
+             ? plain_kernel(c.K, c.vec_width, c.cache_policy, c.order, p.at_a_time / d.num_cus,
+                            c.bytes)
              : lds_kernel(c.kind, c.K, c.cache_policy, c.bytes >= kFarBytes);
   if (!p.fn) return fail(SWEEP_EINVAL, "no kernel for this cell");
   p.grid = p.plan.pub.grid_wgs;
@@ -1034,7 +1036,7 @@ int plan_groups(const std::vector<Prepared>& ps, bool fuse, std::vector<LaunchGr
       const bool far = std::any_of(ps.begin() + i, ps.begin() + j,
                                    [](const Prepared& p) { return p.c.bytes >= kFarBytes; });
       const void* fn = fused_kernel(p0.c.K, p0.c.vec_width, p0.c.cache_policy,
-                                    p0.plan.pub.waves, far);
+                                    p0.at_a_time, far);
       int nb = 0;
       if (fn) HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fn, (int)p0.threads,
                                                                    p0.lds));

@@ -167,3 +167,22 @@ for V in (4, 8, 16):
         assert got[case[:-1] + "0"][1] == forms, case
         spaced += "spaced" in forms[0]
     assert 0 < spaced < len(got)
+
+
+def test_a_fused_batch_of_several_turns_takes_the_form_of_one(host):
+    """The fused loop's form goes by the bytes in flight: a grid of more
+    workgroups than the CUs hold has no more of them."""
+    got = host("""
+for K, w in ((3, 8), (6, 4), (7, 4), (4, 8)):
+    for turns in (1, 2, 8):
+        cells = [isw.make_cell(buf + (i << 20), 1 << 20, K, 16, w, 1 << 20,
+                               grid_wgs=256 * w // 4 * turns) for i in range(3)]
+        fake.fake_reset()
+        with isw.sweep_graph_create(cells, isw.make_opts(fuse=True)) as g:
+            isw.sweep_graph_launch(g)
+        out[f"{K} {w} {turns}"] = [k[:k.index("ILi")] for k in launched() if "fused" in k]
+""")
+    for case, ran in got.items():
+        K, w, _ = map(int, case.split())
+        back_to_back = K * w <= 24                    # 256 CUs x w waves x K KiB up to 6 MiB
+        assert len(ran) == 1 and ("ahead" in ran[0]) == back_to_back, (case, ran)
