@@ -398,25 +398,29 @@ int sweep_run(const sweep_cell_t* cells, int n, const sweep_opts_t* opt,
 
 /* Batched sweep (no passage of the paper defines it: it batches the cells
  * of Section 3's sweeps the way a production sweep runs them): the same
- * cells captured into a hipGraph (one kernel node per cell, then one
- * finishing node) and launched with a single
- * hipGraphLaunch; equivalent to sweep_graph_create + sweep_graph_launch +
- * sweep_graph_destroy.  Per-cell windows come from the in-kernel clock
+ * cells as one replay, equivalent to sweep_graph_create +
+ * sweep_graph_launch + sweep_graph_destroy: more than four launches are
+ * captured into a hipGraph (one kernel node per launch, then one finishing
+ * node) and go out with a single hipGraphLaunch, up to four, a fused batch
+ * of one configuration among them, as launches.  Per-cell windows come from the in-kernel clock
  * records; results[i].event_ms is 0 and *graph_ms receives the hipEvent
  * time of the whole launch.  Errors as sweep_run. */
 int sweep_batched(const sweep_cell_t* cells, int n, const sweep_opts_t* opt,
                   sweep_result_t* results, double* graph_ms);
 
-/* A sweep captured once into a hipGraph and replayed (as sweep_batched, no
- * passage of the paper defines it): one kernel node per cell, in order,
- * then one finishing kernel.  (Up to four launches replay faster as launches
- * on the stream, and do so, with the same results.)  The graph owns its scratch
+/* A sweep prepared once and replayed (as sweep_batched, no passage of the
+ * paper defines it): one launch per cell, or per fused run of cells, in
+ * order, then one finishing kernel.  More than four launches are captured
+ * into a hipGraph and replayed with one hipGraphLaunch.  Up to four (so also
+ * every fused batch of one configuration) are not: they replay faster as
+ * launches on the stream, 16 against 31 us for one, with the same results.
+ * The graph owns its scratch
  * (wave records, per-cell results, offsets; 32 B per wave plus 40 B per
  * cell), so other library calls between replays do not disturb it.  The
  * cells' buffers must stay allocated until the graph is destroyed; their
  * contents may change between replays.
- * sweep_graph_create: validates every cell (errors as sweep_run), captures
- *   and instantiates; *out receives the handle.  Only opt->pin_occupancy
+ * sweep_graph_create: validates every cell (errors as sweep_run), plans the
+ *   launches, and captures and instantiates more than four; *out receives the handle.  Only opt->pin_occupancy
  *   and opt->fuse are read (opt may be NULL).  SWEEP_ENOMEM if the scratch
  *   cannot be had.
  * sweep_graph_launch: replays on `stream` (a hipStream_t of the graph's

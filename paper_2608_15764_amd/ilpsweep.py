@@ -420,7 +420,8 @@ def sweep_run(cells, opts=None, raw=False):
 
 
 def sweep_batched(cells, opts=None, raw=False):
-    """Capture ``cells`` into a hipGraph, launch it once, destroy it; (results, graph ms)."""
+    """One replay of ``cells`` as by :func:`sweep_graph_create`, which is then destroyed
+    (more than four launches go out as one hipGraph); (results, replay ms)."""
     arr = cell_array(cells)
     res = (sweep_result_t * len(arr))()
     o = opts if opts is not None else make_opts()
@@ -431,7 +432,8 @@ def sweep_batched(cells, opts=None, raw=False):
 
 
 class SweepGraph:
-    """Handle of a captured sweep: the C handle and its cell count.  Usable
+    """Handle of a prepared sweep (a captured hipGraph if it has more than four
+    launches): the C handle and its cell count.  Usable
     as a context manager that destroys the graph on exit."""
 
     def __init__(self, handle, n):

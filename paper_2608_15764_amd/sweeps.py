@@ -15,8 +15,9 @@ path_comparison    Section 4.3: LDS-direct loads against the matched
 two_stream         Section 4.4: two co-resident streams in one workgroup,
                    displacement against each stream running solo.
 batched_autotuned  64 uneven sweep points with per-size-class tuned
-                   (vector width, K, waves, cache policy), captured in one
-                   hipGraph, against the same points launched one by one
+                   (vector width, K, waves, cache policy), replayed as fused
+                   persistent launches (in one hipGraph if there are more
+                   than four), against the same points launched one by one
                    at the untuned default.
 precision_sum      streaming FP32 / BF16 / FP8 sum with compensated FP32
                    accumulation and an FP64 final combine.
@@ -418,10 +419,11 @@ def batched_autotuned(n_points=64, n=10, default=(16, 2, 16, isw.CACHE_BYPASS_L1
                       hi_log2=31, fixed=None):
     """64 sweep points of uneven size (1 MiB .. 2 GiB), laid out back to
     back in one seeded buffer, each read once per pass at its size class's
-    tuned (V, K, waves, policy): captured once as a hipGraph, in which the
+    tuned (V, K, waves, policy): prepared once as a graph, in which the
     consecutive points of one tuned configuration run as one fused
-    persistent launch, and replayed ``n`` times; against the same graph
-    with one kernel node per point, and the same points launched one by one
+    persistent launch (one configuration for all of them is one launch, which
+    is replayed as a launch and not as a hipGraph), and replayed ``n`` times;
+    against the same graph with one kernel node per point, and the same points launched one by one
     at the untuned default.  ``verify``, if given, is called with one (seed, first word,
     words, sum32, xor32) tuple per launch of the first tuned replay and of
     the first untuned pass, and returns one bool per tuple: whether those
