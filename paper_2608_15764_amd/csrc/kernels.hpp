@@ -252,7 +252,9 @@ constexpr double kGateSeconds = 200e-6;   // a host that takes longer is timed w
 hipError_t launch_gate(const GateArgs& a, hipStream_t st, hipEvent_t done);
 hipError_t launch_read_clock(uint64_t* out, hipStream_t st);
 // 16-byte loads of a lane's group: 8 at one wave per SIMD, 4 above, so that
-// at least 8 MiB can be in flight at every occupancy of the default grid.
+// the forms that ask for a whole group at a time, or keep one in flight, have
+// at least 8 MiB in flight at every occupancy of the default grid.  (Those for
+// many waves ask for one or two loads at a time, 6 MiB and more.)
 constexpr int reduce_loads(int waves_per_cu) { return waves_per_cu == 4 ? 8 : 4; }
 // in the form for n_waves waves over `bytes`
 const void* reduce_kernel(int dtype, int waves_per_cu, uint64_t n_waves, uint64_t bytes);

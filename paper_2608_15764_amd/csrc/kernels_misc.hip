@@ -464,8 +464,8 @@ __global__ __launch_bounds__(256) void reduce_fp(ReduceArgs a) {
   reduce_body<DT, NL, NL>(a);
 }
 // The ring is for BF16 at one or two waves per SIMD.  There the arithmetic of
-// a group (64 TwoSums per load of a lane) takes as long as its loads, and no
-// other wave covers either: 4 GiB at 4 waves per CU 5.75 -> 7.25 TB/s, at 8
+// a group (eight TwoSums per load of a lane, 64 or 32 a group) takes as long as
+// its loads, and no other wave covers either: 4 GiB at 4 waves per CU 5.75 -> 7.25 TB/s, at 8
 // 7.25 either way; 1 GiB 5.3 -> 7.0 and 6.9 -> 7.1; 64 MiB 4.3 -> 5.3 and 5.2 ->
 // 5.6.  FP32 and FP8 have fewer operations per byte and read 2 % faster in
 // batches at 4 waves (7.39 against 7.17 TB/s over 4 GiB); from 12 waves per CU
@@ -512,6 +512,8 @@ const void* reduce_few_of(int dtype) {
 // 512 MiB 32 waves gain nothing (FP32 and BF16 1 % slower), so their line is
 // there; over 128 MiB most lose 1-5 %.
 const void* reduce_kernel(int dtype, int waves_per_cu, uint64_t n_waves, uint64_t bytes) {
+  // (with eight loads BF16 always takes the ring; reduce_of<8> holds it beside
+  // the other types for the audit of the loops' assembly)
   const bool ring = dtype == SWEEP_BF16 && waves_per_cu <= 8;
   if (reduce_loads(waves_per_cu) == 8)
     return ring ? reinterpret_cast<const void*>(&reduce_bf16_ring<8>) : reduce_of<8>(dtype);
