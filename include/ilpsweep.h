@@ -426,7 +426,8 @@ int sweep_batched(const sweep_cell_t* cells, int n, const sweep_opts_t* opt,
  * sweep_graph_launch: replays on `stream` (a hipStream_t of the graph's
  *   device, NULL = default stream), waits, and fills results[0..n) in cell
  *   order (per-cell windows from the in-kernel clock records, event_ms 0)
- *   and *graph_ms (hipEvent time of the whole replay; may be NULL).
+ *   and *graph_ms (hipEvent time of the whole replay, from an event in front
+ *   of it, so with what the host takes to the first launch; may be NULL).
  *   Replays of one graph must not overlap.
  * sweep_graph_destroy: frees the graph and its scratch; NULL is allowed. */
 typedef struct sweep_graph sweep_graph_t;
